@@ -2008,13 +2008,74 @@ GL_HD bool arc_rule(const DirectArc& T, int N, int g, int G, double& out, Reduce
 // maximum of r^2 close to the far direction.  The trapezoid runs in
 // psi with tan(p/2) = kap tan(psi/2), p measured from that maximum, which
 // spreads the complex zeros of 1 - r^2 at distance b from it to 2 artanh of
-// sqrt(tanh(b/2)) (kap^2 = tanh(b/2)); half order h, G lanes as above.
+// sqrt(tanh(b/2)) (kap^2 = tanh(b/2)); half order h, G lanes as above.  A large
+// shadow can be as close to the limb on its far side: there both pairs of zeros
+// decide the map and the order (near_map).
 struct DirectWhole {
     double a, b, e, f, g0, P0, l1, l2, kap;
     int h;
 };
 constexpr float kNearRate = 34.0f;
 constexpr int kNearMaxHalf = kHalfSteps;
+constexpr float kLargeK = 0.2f;  // up to here a shadow's far side is far from the limb
+
+// Node map of a large shadow's whole ellipse and the distance d of its nearest
+// singularity from the real psi axis.  (b, c, -b, e): the monic quartic without
+// real zeros; t: its maximum's place, t +- i sqrt(im2) about its nearest zeros.
+// In T = tan(p/2) the singularities are the quartic's two pairs and T = i
+// (p = i inf); one at T = x + i y lies at atanh(2 y kap / (kap^2 + |T|^2)) in
+// psi.
+GL_HD bool near_map(double b, double c, double e, double t, double im2, double& kap, float& d)
+{
+    GL_AS_WRITTEN
+    // the quartic as (t^2 + B t + C)(t^2 + B2 t + C2): Newton steps on its
+    // linear and constant coefficients
+    double B = -2.0 * t, C = fma(t, t, im2), B2 = b - B, C2 = 0.0, dB = 0.0, dC = 0.0;
+#pragma unroll 1
+    for (int it = 0; it < 4; ++it) {
+        B2 = b - B;
+        C2 = fma(-B, B2, c - C);
+        const double f = fma(B, C2, fma(B2, C, b)), g = fma(C, C2, -e), cb = B - B2;
+        const double fB = fma(B, cb, C2 - C), fC = B2 - B, gB = C * cb, gC = C2 - C;
+        const double det = fma(fB, gC, -fC * gB), id = rcp(det != 0.0 ? det : 1.0);
+        dB = fma(f, gC, -g * fC) * id;
+        dC = fma(g, fB, -f * gB) * id;
+        B -= dB;
+        C -= dC;
+    }
+    B2 = b - B;
+    C2 = fma(-B, B2, c - C);
+    const double v1 = fma(-0.25 * B, B, C), v2 = fma(-0.25 * B2, B2, C2);
+    if (!(v1 > 0.0 && v2 > 0.0 && fabs(dC) <= 1e-3 * v1 && fabs(dB) * fabs(dB) <= 1e-6 * v1)) return false;
+    // T of a zero u + i v, v = sqrt(vv): (z - t) / (1 + t z)
+    auto place = [&](double u, double vv, float& y, float& n) {
+        const double m = u - t, w = fma(t, u, 1.0), it = rcp(fma(w, w, t * t * vv));
+        y = (float)(sqrt_nn(vv) * fma(t, t, 1.0) * it);
+        n = (float)(fma(m, m, vv) * it);
+    };
+    float y1, n1, y2, n2;
+    place(-0.5 * B, v1, y1, n1);
+    place(-0.5 * B2, v2, y2, n2);
+    // tanh of the distance for kap^2 = q
+    auto reach = [&](float q) {
+        return 2.0f * sqrt_f(q) * fminf(fminf(y1 * rcp_f(q + n1), y2 * rcp_f(q + n2)), rcp_f(q + 1.0f));
+    };
+    // the first pair as far as T = i, or as the second pair
+    float best = 0.0f, qb = 1.0f;
+    const float cand[3] = {1.0f, (y1 - n1) * rcp_f(fmaxf(1.0f - y1, 1e-6f)), (y1 * n2 - y2 * n1) * rcp_f(y2 != y1 ? y2 - y1 : 1e-6f)};
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const float q = cand[i], r = q > 1e-12f && q < 1e6f ? reach(q) : 0.0f;
+        if (r > best) {
+            best = r;
+            qb = q;
+        }
+    }
+    kap = sqrt_nn((double)qb);
+    const float x = fminf(best, 0.9999f);
+    d = 0.5f * log_f((1.0f + x) * rcp_f(1.0f - x));
+    return best > 0.0f;
+}
 
 template <class SH>
 GL_HD bool direct_whole(const SH& s, double x0, double y0, DirectWhole& T)
@@ -2023,7 +2084,7 @@ GL_HD bool direct_whole(const SH& s, double x0, double y0, DirectWhole& T)
     const double rho2 = fma(x0, x0, y0 * y0);
     const double K0 = fma(0.5, s.M2, rho2 - 1.0), K1 = 2.0 * fma(x0, s.A, y0 * s.B), K2 = 2.0 * y0 * s.C;
     const double n2 = fma(K1, K1, K2 * K2);
-    if (!(n2 > 1e-20) || large_and_flat((float)s.k, (float)(s.AC / s.k))) return false;
+    if (!(n2 > 1e-20)) return false;
     const double ir = rsqrt_n(n2), ca = K1 * ir, sa = K2 * ir, R1 = n2 * ir;  // far direction: t = 0
     const double c2a = fma(ca, ca, -sa * sa), s2a = 2.0 * ca * sa;
     const double K3r = fma(s.K3, c2a, s.K4 * s2a), K4r = fma(s.K4, c2a, -s.K3 * s2a);
@@ -2055,14 +2116,19 @@ GL_HD bool direct_whole(const SH& s, double x0, double y0, DirectWhole& T)
     const double it2 = rcp(fma(t, t, 1.0)), cu = fma(-t, t, 1.0) * it2, su = 2.0 * t * it2;
     const double cc = fma(cu, ca, -su * sa), sc = fma(su, ca, cu * sa);
     // (the zeros of the quartic close to the maximum are about t +- i sqrt(im2);
-    // the others follow from the roots' sum and product and must stay away)
+    // the others follow from the roots' sum and product)
     const double im2 = 2.0 * pv * rcp(pp), t2 = -0.5 * b - t, jm2 = fma(-t2, t2, e * rcp(fma(t, t, im2)));
-    const double tn = fma(t2, t2, 1.0);
-    if (!(jm2 > 0.3 * tn * tn)) return false;
-    const double beta = fmin(sqrt_nn(im2) * it2, 0.9);  // about tanh(b/2)
-    T.kap = sqrt_nn(beta);
-    const float kf = (float)T.kap;
-    const float d = log_f((1.0f + kf) * rcp_f(1.0f - kf));  // 2 artanh(kap)
+    float d;
+    if ((float)s.k > kLargeK) {
+        if (!near_map(b, c, e, t, im2, T.kap, d)) return false;
+    } else {
+        const double tn = fma(t2, t2, 1.0);
+        if (!(jm2 > 0.3 * tn * tn)) return false;  // the others are far
+        const double beta = fmin(sqrt_nn(im2) * it2, 0.9);  // about tanh(b/2)
+        T.kap = sqrt_nn(beta);
+        const float kf = (float)T.kap;
+        d = log_f((1.0f + kf) * rcp_f(1.0f - kf));  // 2 artanh(kap)
+    }
     const float hn = 0.5f * kNearRate * rcp_f(fmaxf(d, 1e-3f));
     if (!(hn <= (float)kNearMaxHalf)) return false;
     T.h = (int)ceilf(hn);

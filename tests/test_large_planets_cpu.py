@@ -1,0 +1,127 @@
+"""The direct rules of one sub-sample over the whole range of planets that the
+interface accepts (semi-axes up to the star's), against the general path on the
+same samples (host build), and the oracle where the two differ most.
+
+Samples: ellipses anywhere on the disk, within 1e-9 to 0.3 of touching the limb
+from inside, and about the star's centre, where a large planet is close to the
+limb on both sides.
+
+Tolerance: the exact path's bar of 1e-9 on every accepted sample.  The rules'
+orders aim at exp(-31) and better; the general path's own error is below 1e-9.
+"""
+import os
+import shutil
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+from paper_2410_05408_amd import workloads as W
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIP_INC = "/opt/rocm/include"
+TOL = 1e-9
+ARS, PERIOD = 200.0, 500.0
+
+
+@pytest.fixture(scope="module")
+def check(tmp_path_factory):
+    cxx = shutil.which("g++")
+    if cxx is None or not os.path.exists(os.path.join(HIP_INC, "hip", "hip_runtime.h")):
+        pytest.skip("needs g++ and the HIP headers")
+    exe = str(tmp_path_factory.mktemp("host") / "gl_direct_check")
+    subprocess.run([cxx, "-O2", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", HIP_INC,
+                    "-I", os.path.join(ROOT, "paper_2410_05408_amd", "csrc"), "-I", os.path.join(ROOT, "include"),
+                    os.path.join(ROOT, "tests", "host", "gl_direct_check.cpp"), "-o", exe], check=True)
+    return exe
+
+
+def run(check, tmp_path, p, t):
+    pf, tf, of = (str(tmp_path / f) for f in ("p.bin", "t.bin", "o.bin"))
+    np.ascontiguousarray(p).tofile(pf)
+    np.ascontiguousarray(t).tofile(tf)
+    subprocess.run([check, pf, tf, of], check=True)
+    return np.fromfile(of).reshape(3, t.size)
+
+
+def oracle_flux(p, t):
+    # in a process of its own: the oracle counts integrals that stop above
+    # their target, which other tests read
+    code = ("import sys, numpy as np; from oracle import glo; a = np.load(sys.argv[1]); n = a.shape[1]; "
+            "f = glo.flux_batch if a.shape[0] == 11 else glo.flux_batch_ell; "
+            "np.save(sys.argv[1], f(np.ascontiguousarray(a[:-1]), np.ascontiguousarray(a[-1]), offsets=np.arange(n + 1), "
+            "n_ss=np.ones(n, np.int32), t_exp=np.zeros(n)).reshape(-1))")
+    import tempfile
+    with tempfile.TemporaryDirectory() as d:
+        path = os.path.join(d, "a.npy")
+        np.save(path, np.concatenate([p, t[None, :]]))
+        subprocess.run([sys.executable, "-c", code, path], check=True, cwd=ROOT)
+        return np.load(path)
+
+
+def planets(rng, n, k_lo, k_hi):
+    p = np.zeros((10, n))
+    p[W.K], p[W.F] = rng.uniform(k_lo, k_hi, n), rng.uniform(0.0, 0.95, n)
+    p[W.THETA], p[W.PHI] = rng.uniform(0.0, np.pi, n), rng.uniform(0.0, 2.0 * np.pi, n)
+    p[W.ARS], p[W.P] = ARS, PERIOD
+    p[W.Q1], p[W.Q2] = rng.uniform(0.0, 1.0, n), rng.uniform(0.0, 1.0, n)
+    return p
+
+
+def semi_axes(p):
+    """Projected semi-axes and the minor axis' direction on the sky."""
+    k, f, th, ph = p[W.K], p[W.F], p[W.THETA], p[W.PHI]
+    minor = k * np.sqrt(np.cos(th) ** 2 + (1.0 - f) ** 2 * np.sin(th) ** 2)
+    return k, minor, np.cos(ph), -np.sin(ph)
+
+
+def placed(p, x, y):
+    """Impact parameters and times that put the centres at (x, y)."""
+    al = np.arcsin(y / ARS)
+    p[W.B] = x / np.cos(al)
+    return p, al * PERIOD / (2.0 * np.pi)
+
+
+def samples(kind, n, k_lo, k_hi, seed=41):
+    rng = np.random.default_rng(seed)
+    p = planets(rng, n, k_lo, k_hi)
+    a = rng.uniform(0.0, 2.0 * np.pi, n)
+    ca, sa = np.cos(a), np.sin(a)
+    if kind == "disk":
+        r = rng.uniform(0.0, 1.0, n) * (1.0 + p[W.K])
+    elif kind == "centre":
+        r = 10.0 ** rng.uniform(-9.0, -1.0, n)
+    else:  # the farthest point of the ellipse at 1 - eps
+        eps = 10.0 ** rng.uniform(-9.0, -0.5, n)
+        maj, mnr, ux, uy = semi_axes(p)
+        th = np.linspace(0.0, 2.0 * np.pi, 257)[:-1, None]
+        ex = maj * np.cos(th) * -uy + mnr * np.sin(th) * ux
+        ey = maj * np.cos(th) * ux + mnr * np.sin(th) * uy
+        lo, hi = np.zeros(n), np.ones(n)
+        for _ in range(40):
+            m = 0.5 * (lo + hi)
+            out = np.max((m * ca + ex) ** 2 + (m * sa + ey) ** 2, axis=0) > (1.0 - eps) ** 2
+            lo, hi = np.where(out, lo, m), np.where(out, m, hi)
+        r = lo
+    return placed(p, r * ca, r * sa)
+
+
+def compare(check, tmp_path, p, t):
+    direct, general, cls = run(check, tmp_path, p, t)
+    assert np.all(np.isfinite(general))
+    took = np.isfinite(direct) & (cls != -2)
+    diff = np.where(took, np.abs(direct - general), 0.0)
+    assert diff.max() <= TOL
+    worst = np.argsort(diff)[-50:]
+    ref = oracle_flux(np.ascontiguousarray(p[:, worst]), t[worst])
+    assert np.abs(direct[worst] - ref)[took[worst]].max() <= TOL
+    return took, cls
+
+
+@pytest.mark.parametrize("kind", ["disk", "limb", "centre"])
+@pytest.mark.parametrize("k_lo,k_hi", [(0.5, 0.8), (0.8, 0.95), (0.95, 0.999)])
+def test_large_planets(check, tmp_path, kind, k_lo, k_hi):
+    p, t = samples(kind, 20000, k_lo, k_hi)
+    took, cls = compare(check, tmp_path, p, t)
+    assert took.sum() > 2000
