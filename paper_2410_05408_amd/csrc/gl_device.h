@@ -1753,19 +1753,71 @@ struct DirectArc {
     double al, k;           // node map
     double base;            // occulted fraction without the mu^3 integral
     int N;                  // trapezoid intervals
-    bool large;
 };
 enum DirectStatus : int { DIRECT_DECLINED = 0, DIRECT_OFF = 1, DIRECT_ARC = 2 };
 
 // The rule's order: error exp(-2 N a) on the arc, tolerance on the change from
 // the rule of half the order (whose error is the square root of the rule's).
-// Large flat shadows (k > 0.2, minor below half the major semi-axis) can have
-// the quartic's other zeros closer than the singularities the order is taken
-// from: a larger exponent there.
-constexpr float kArcRate = 31.0f, kArcRateFlat = 46.0f;
-GL_HD bool large_and_flat(float k, float kq) { return k > 0.2f && kq < 0.5f * k; }
+// Up to k = 0.2 the zeros of r^2 and the arc's ends across the gap are the
+// nearest singularities; a larger or flatter shadow can have the quartic's
+// complex pair nearer, which then enters the order (pair_axis).  The zeros of r^2 are poles,
+// and closer to a large shadow's arc: from k = 0.35 on the exponent grows with k,
+// which keeps the error below the general path's (rms, k 0.7 to 0.9: 4e-14 here,
+// 5e-14 there, 1e-12 at a fixed exponent of 31).
+constexpr float kArcRate = 31.0f, kArcRateK = 20.0f;
+GL_HD bool large_or_flat(float k, float kq) { return k > 0.2f || kq < 0.05f * k; }
 constexpr int kArcMaxN = 256;
-constexpr double kArcCheck = 2e-5, kArcCheckLarge = 6e-5;  // up to k = 0.2, above
+constexpr double kArcCheck = 2e-5;
+
+// Half the sum of y's distances from -1 and 1, the major semi-axis of the
+// ellipse with these foci through y (phi = acos(y) is acosh(a) from the real
+// axis there).
+GL_HD float foci_axis(float yr, float yi)
+{
+    const float i2 = yi * yi, p = yr + 1.0f, m = yr - 1.0f;
+    return 0.5f * (sqrt_f(fmaf(p, p, i2)) + sqrt_f(fmaf(m, m, i2)));
+}
+
+// Principal square root of a complex number.
+GL_HD void csqrt_f(float x, float y, float& re, float& im)
+{
+    const float big = sqrt_f(0.5f * (sqrt_f(fmaf(x, x, y * y)) + fabsf(x))), small = 0.5f * y * rcp_f(fmaxf(big, 1e-20f));
+    re = x >= 0.0f ? big : fabsf(small);
+    im = x >= 0.0f ? small : copysignf(big, y);
+}
+
+// The quartic's complex zeros t = zr +- i zi as singularities of the arc rule:
+// the smallest foci_axis of their images in y.  (cp, sp): the arc's centre in
+// psi; ih = 1 / tan(delta/4); k: the node map.  p and p + 2 pi are the same
+// point, so tan(p/4) has the images E and -1/E; the map takes y and -1/(k y) to
+// the same x.
+GL_HD float pair_axis(float zr, float zi, float cp, float sp, float ih, float k)
+{
+    // half of the centre's angle, then T = tan(p/2), E = tan(p/4)
+    const float big = sqrt_f(fmaf(0.5f, fabsf(cp), 0.5f)), small = 0.5f * sp * rcp_f(big);
+    const float c = cp >= 0.0f ? big : fabsf(small), s = cp >= 0.0f ? small : copysignf(big, sp);
+    const float nr = fmaf(zr, c, -s), ni = zi * c, dr = fmaf(zr, s, c), di = zi * s;
+    const float id = rcp_f(fmaxf(fmaf(dr, dr, di * di), 1e-20f));
+    const float Tr = fmaf(nr, dr, ni * di) * id, Ti = fmaf(ni, dr, -nr * di) * id;
+    float qr, qi;
+    csqrt_f(fmaf(Tr, Tr, fmaf(-Ti, Ti, 1.0f)), 2.0f * Tr * Ti, qr, qi);
+    qr += 1.0f;
+    const float iq = rcp_f(fmaf(qr, qr, qi * qi));
+    const float Er = fmaf(Tr, qr, Ti * qi) * iq, Ei = fmaf(Ti, qr, -Tr * qi) * iq;
+    const float ie = rcp_f(fmaxf(fmaf(Er, Er, Ei * Ei), 1e-20f)), om = 1.0f - k;
+    float a = 1e20f;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const float xr = (i ? Er * ie : Er) * ih, xi = (i ? Ei * ie : Ei) * ih;
+        csqrt_f(fmaf(om, om, 4.0f * k * fmaf(xr, xr, -xi * xi)), 8.0f * k * xr * xi, qr, qi);
+        qr += om;
+        const float r = 2.0f * rcp_f(fmaxf(fmaf(qr, qr, qi * qi), 1e-20f));
+        const float yr = fmaf(xr, qr, xi * qi) * r, yi = fmaf(xi, qr, -xr * qi) * r;
+        const float o = rcp_f(fmaxf(k * fmaf(yr, yr, yi * yi), 1e-20f));
+        a = fminf(a, fminf(foci_axis(yr, yi), foci_axis(yr * o, yi * o)));
+    }
+    return a;
+}
 
 // Two crossings.  The quartic of the crossings in t = tan(psi/2), psi = th -
 // th0, has a1 = -a3 when th0 is the direction of the farthest or the nearest
@@ -1927,11 +1979,16 @@ GL_HD int direct_arc(const SH& s, double c0l, double c2l, double inv_phi, double
     const float eta = 2.0f * ze * rcp_f(om + sqrt_f(fmaxf(fmaf(om, om, -4.0f * ze * (ze * kk)), 0.0f)));
     const float yr = 2.0f * Z * rcp_f(om + sqrt_f(fmaf(om, om, 4.0f * Z * (Z * kk))));
     const float re = eta + sqrt_f(fmaf(eta, eta, 1.0f)), rr = yr + sqrt_f(fmaxf(fmaf(yr, yr, -1.0f), 0.0f));
-    const float rate = log_f(fminf(re, rr));
-    T.large = kf > 0.2f;
+    float near = fminf(re, rr), exponent = kArcRate;
+    if (large_or_flat(kf, kqf)) {
+        const float ax = fmaxf(pair_axis(tc, 0.5f * sqrt_f(im2), (float)cp, (float)sp, ih, kk), 1.0f);
+        near = fminf(near, ax + sqrt_f(fmaf(ax, ax, -1.0f)));
+        exponent = fmaf(kArcRateK, fmaxf(kf - 0.35f, 0.0f), kArcRate);
+    }
+    const float rate = log_f(near);
     T.k = (double)kk;
     T.al = h4 * (1.0 - T.k);
-    const float Nh = 0.25f * (large_and_flat(kf, kqf) ? kArcRateFlat : kArcRate) * rcp_f(fmaxf(rate, 1e-3f));
+    const float Nh = 0.25f * exponent * rcp_f(fmaxf(rate, 1e-3f));
     T.N = Nh <= (float)(kArcMaxN / 2) ? 2 * (int)ceilf(Nh) : kArcMaxN + 2;
     if (T.N < 6) T.N = 6;
     return T.N <= kArcMaxN ? DIRECT_ARC : DIRECT_DECLINED;
@@ -2001,7 +2058,7 @@ GL_HD bool arc_rule(const DirectArc& T, int N, int g, int G, double& out, Reduce
     even = reduce(even);
     const double f = 4.0 * T.al * kPi * rcp((double)N);
     out = f * all;
-    return fabs(f * fma(-2.0, even, all)) <= (T.large ? kArcCheckLarge : kArcCheck);
+    return fabs(f * fma(-2.0, even, all)) <= kArcCheck;
 }
 
 // A whole ellipse too near the limb for the class bound: no crossing, one
@@ -2017,7 +2074,6 @@ struct DirectWhole {
 };
 constexpr float kNearRate = 34.0f;
 constexpr int kNearMaxHalf = kHalfSteps;
-constexpr float kLargeK = 0.2f;  // up to here a shadow's far side is far from the limb
 
 // Node map of a large shadow's whole ellipse and the distance d of its nearest
 // singularity from the real psi axis.  (b, c, -b, e): the monic quartic without
@@ -2119,7 +2175,7 @@ GL_HD bool direct_whole(const SH& s, double x0, double y0, DirectWhole& T)
     // the others follow from the roots' sum and product)
     const double im2 = 2.0 * pv * rcp(pp), t2 = -0.5 * b - t, jm2 = fma(-t2, t2, e * rcp(fma(t, t, im2)));
     float d;
-    if ((float)s.k > kLargeK) {
+    if (large_or_flat((float)s.k, (float)(s.AC / s.k))) {
         if (!near_map(b, c, e, t, im2, T.kap, d)) return false;
     } else {
         const double tn = fma(t2, t2, 1.0);

@@ -125,3 +125,44 @@ def test_large_planets(check, tmp_path, kind, k_lo, k_hi):
     p, t = samples(kind, 20000, k_lo, k_hi)
     took, cls = compare(check, tmp_path, p, t)
     assert took.sum() > 2000
+
+
+@pytest.mark.parametrize("k_lo,k_hi", [(0.5, 0.7), (0.7, 0.9), (0.9, 0.999)])
+def test_crossing_arcs(check, tmp_path, k_lo, k_hi):
+    # no further from the oracle than the general path, which they replace
+    p, t = samples("disk", 12000, k_lo, k_hi, seed=7)
+    direct, general, cls = run(check, tmp_path, p, t)
+    m = np.isfinite(direct) & (cls == -1)
+    assert m.sum() > 2000
+    ref = oracle_flux(np.ascontiguousarray(p[:, m]), t[m])
+    rms = lambda f: np.sqrt(np.mean((f[m] - ref) ** 2))
+    assert rms(direct) <= rms(general)
+
+
+@pytest.mark.parametrize("locked", [False, True])
+def test_large_ellipsoids(check, tmp_path, locked):
+    rng = np.random.default_rng(43)
+    n = 20000
+    p = W.draw_ellipsoids(rng, n, locked)
+    p[:3] = 10.0 ** rng.uniform(-1.0, np.log10(0.99), (3, n))
+    k = np.max(p[:3], axis=0)
+    p[W.E_ARS] = rng.uniform(2.5, 20.0, n)
+    p[W.E_B] = rng.uniform(0.0, 1.0, n)
+    reach = np.arcsin(np.minimum(1.0, (1.0 + k) / p[W.E_ARS])) / (2.0 * np.pi) * p[W.E_P]
+    took, cls = compare(check, tmp_path, p, p[W.E_T0] + rng.uniform(-1.0, 1.0, n) * reach)
+    assert took.sum() > 4000
+
+
+def test_known_samples(check, tmp_path):
+    # close to the limb on both sides: off by 4.0e-7 with an order from the near
+    # side's zeros alone; a needle (f = 0.999996), off by 3.8e-10 with an order
+    # without the quartic's complex pair
+    p = np.array([[0.960440290366926, 0.47358153665846714, 1.7029063907121635, 6.160755649334051, 0.0034152288856442643,
+                   201.77358757001537, 500.0, 0.0, 0.81225802445182, 0.028127730765128867],
+                  [0.19752358398605882, 0.99999579031346308, 1.5853178409309001, 4.2426871421488102, 0.0, 200.0, 500.0, 0.0,
+                   1.0, 0.5]]).T
+    q, t1 = placed(np.ascontiguousarray(p[:, 1:]), np.array([-0.4746243309247809]), np.array([0.85719980323387412]))
+    p = np.concatenate([p[:, :1], q], axis=1)
+    t = np.array([0.008177178922197671, t1[0]])
+    direct, general, _ = run(check, tmp_path, p, t)
+    assert np.abs(direct - oracle_flux(p, t)).max() <= 1e-11
