@@ -1205,7 +1205,7 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
                         double x0, y0;
                         const gl::Shape sh = entry(v0, x0, y0);
                         gl::DirectArc T;
-                        const int st = gl::direct_arc(sh, S.c0, S.c2, S.inv_phi, x0, y0, T);
+                        const int st = gl::direct_arc(sh, S.c0, S.c1, S.c2, S.inv_phi, x0, y0, T);
                         lap(C_HARD);
                         double F = 1.0;
                         bool ok = st == gl::DIRECT_OFF;

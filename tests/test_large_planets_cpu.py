@@ -125,6 +125,10 @@ def test_large_planets(check, tmp_path, kind, k_lo, k_hi):
     p, t = samples(kind, 20000, k_lo, k_hi)
     took, cls = compare(check, tmp_path, p, t)
     assert took.sum() > 2000
+    if kind == "disk":
+        # outlines around the star's centre are accepted (they and those near
+        # it, which can take too long an order, are 0.15 to 0.65 of the samples)
+        assert np.sum(cls[~took] == -1) <= 0.15 * np.sum(cls != -2)
 
 
 @pytest.mark.parametrize("k_lo,k_hi", [(0.5, 0.7), (0.7, 0.9), (0.9, 0.999)])
