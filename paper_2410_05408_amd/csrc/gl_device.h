@@ -535,15 +535,12 @@ GL_HD double phase_time(const OB& s, double t)
     return fma(-s.P, rint(dt * s.inv_P), dt);
 }
 
-// Per-sample shadow of a locked set at time t (Appendix B): body coordinates
-// R Rx(-alpha) Ry(beta) (x - x_c) at the sample's orbital phase alpha; the
-// centre follows from centre_at with the same alpha.
-GL_HD void lock_at(const SetConst& s, double t, SetConst& o)
+// Per-sample shadow of a locked set (Appendix B): body coordinates
+// R Rx(-alpha) Ry(beta) (x - x_c) at the orbital phase alpha whose sine and
+// cosine are sa, ca.
+GL_HD void lock_turned(const SetConst& s, double sa, double ca, SetConst& o)
 {
     o = s;
-    const double alpha = s.w_orb * phase_time(s, t);
-    double sa, ca;
-    sincos_pi(alpha, sa, ca);
     const double sb = s.sb, cb = s.cb;
     double u[3], v[3], w[3];
     for (int i = 0; i < 3; ++i) {
@@ -556,6 +553,14 @@ GL_HD void lock_at(const SetConst& s, double t, SetConst& o)
     deltas_of_map(s.ax2, u, v, w, o.A, o.B, o.C);
     const double kmaj = shadow_axes(o.A, o.B, o.C, o.sx, o.sy);
     shape_terms(o, kmaj);
+}
+
+// The same at time t; the centre follows from centre_at with the same phase.
+GL_HD void lock_at(const SetConst& s, double t, SetConst& o)
+{
+    double sa, ca;
+    sincos_pi(s.w_orb * phase_time(s, t), sa, ca);
+    lock_turned(s, sa, ca, o);
 }
 
 // ---------------------------------------------------------------- work census
@@ -937,7 +942,11 @@ GL_HD double gk_piece(const Frame& F, double cc, double sc, double mid, double h
         }
         node(20, std::false_type{});
     } else {
-#pragma unroll 1
+        // (three at a time: a lone wavefront waits on a single node's chain, 64
+        // sets of 1000 outputs, k 0.6 to 0.8: 132 us, 128 with three; seven make
+        // it 108, but take registers that the fused pass then saves around its
+        // call: 4096 sets of 1009 x 3 sub-samples 215 -> 221 us)
+#pragma unroll 3
         for (int j = 0; j < 21; ++j) node(j, std::true_type{});
     }
     // dpsi factor 2, f_flat = flat/2, f_lin = (2/3) G flat/2, f_quad = quad/2
@@ -1760,7 +1769,7 @@ enum DirectStatus : int { DIRECT_DECLINED = 0, DIRECT_OFF = 1, DIRECT_ARC = 2 };
 // the rule of half the order (whose error is the square root of the rule's).
 // Up to k = 0.2 the zeros of r^2 and the arc's ends across the gap are the
 // nearest singularities; a larger or flatter shadow can have the quartic's
-// complex pair nearer, which then enters the order (pair_axis).  The zeros of r^2 are poles,
+// complex pair nearer, which then enters the order (images_axis).  The zeros of r^2 are poles,
 // and closer to a large shadow's arc: from k = 0.35 on the exponent grows with k,
 // which keeps the error below the general path's (rms, k 0.7 to 0.9: 4e-14 here,
 // 5e-14 there, 1e-12 at a fixed exponent of 31).
@@ -1815,28 +1824,20 @@ GL_HD float images_axis(float er, float ei, float ih, float k)
     return a;
 }
 
-// tan(p/4) of the quartic's zero t = zr + i zi; (cp, sp): the arc's centre in psi.
-GL_HD void pair_place(float zr, float zi, float cp, float sp, float& er, float& ei)
+// e^(i th) of the quartic's zero t = zr + i zi; (ca, sa): its anchor th0.
+GL_HD void zero_place(float zr, float zi, float ca, float sa, float& ur, float& ui)
 {
-    // half of the centre's angle, then T = tan(p/2)
-    const float big = sqrt_f(fmaf(0.5f, fabsf(cp), 0.5f)), small = 0.5f * sp * rcp_f(big);
-    const float c = cp >= 0.0f ? big : fabsf(small), s = cp >= 0.0f ? small : copysignf(big, sp);
-    const float nr = fmaf(zr, c, -s), ni = zi * c, dr = fmaf(zr, s, c), di = zi * s;
-    const float id = rcp_f(fmaxf(fmaf(dr, dr, di * di), 1e-20f));
-    const float Tr = fmaf(nr, dr, ni * di) * id, Ti = fmaf(ni, dr, -nr * di) * id;
-    float qr, qi;
-    csqrt_f(fmaf(Tr, Tr, fmaf(-Ti, Ti, 1.0f)), 2.0f * Tr * Ti, qr, qi);
-    qr += 1.0f;
-    const float iq = rcp_f(fmaf(qr, qr, qi * qi));
-    er = fmaf(Tr, qr, Ti * qi) * iq;
-    ei = fmaf(Ti, qr, -Tr * qi) * iq;
+    const float n = fmaf(zr, zr, zi * zi), id = rcp_f(fmaf(2.0f, zi, n + 1.0f));
+    const float er = (1.0f - n) * id, ei = 2.0f * zr * id;
+    ur = fmaf(er, ca, -ei * sa);
+    ui = fmaf(ei, ca, er * sa);
 }
 
 // The zeros of r^2 on a shadow's outline, z = e^(i th) from
 // (A + C + i B) z^2 + 2 (x0 + i y0) z + (A - C + i B) = 0, the larger first.
 // Both are inside the unit circle when the shadow encloses the star's centre.
 struct Poles {
-    float r1, i1, r2, i2, m1, m2;  // and their absolute values
+    float r1, i1, r2, i2;
 };
 GL_HD Poles outline_poles(float A, float B, float C, float x, float y)
 {
@@ -1847,16 +1848,14 @@ GL_HD Poles outline_poles(float A, float B, float C, float x, float y)
     const float ar = A + C, ia = rcp_f(fmaf(ar, ar, B * B)), nr = -fmaf(sg, sr, x), ni = -fmaf(sg, si, y);
     z.r1 = fmaf(nr, ar, ni * B) * ia;
     z.i1 = fmaf(ni, ar, -nr * B) * ia;
-    z.m1 = sqrt_f(fmaf(z.r1, z.r1, z.i1 * z.i1));
     // the product of both is (A - C + i B) / (A + C + i B)
-    const float pr = fmaf(A - C, ar, B * B) * ia, pi = 2.0f * B * C * ia, im = rcp_f(fmaxf(z.m1 * z.m1, 1e-20f));
+    const float pr = fmaf(A - C, ar, B * B) * ia, pi = 2.0f * B * C * ia, im = rcp_f(fmaxf(fmaf(z.r1, z.r1, z.i1 * z.i1), 1e-20f));
     z.r2 = fmaf(pr, z.r1, pi * z.i1) * im;
     z.i2 = fmaf(pi, z.r1, -pr * z.i1) * im;
-    z.m2 = fmaxf(sqrt_f(fmaf(z.r2, z.r2, z.i2 * z.i2)), 1e-10f);
     return z;
 }
 
-// tan(p/4) at e^(i th) = zr + i zi; (cc, sc): the arc's centre in th.
+// tan(p/4) where e^(i th) = zr + i zi; (cc, sc): the arc's centre in th.
 GL_HD void pole_place(float zr, float zi, float cc, float sc, float& er, float& ei)
 {
     float ur, ui;  // e^(i p/2)
@@ -1950,9 +1949,12 @@ GL_HD int direct_arc(const SH& s, double c0l, double c1l, double c2l, double inv
     const bool large = large_or_flat(kf, kqf);
     float eb = (rf + sqrt_f(fmaxf(fmaf(rf, rf, -(kf - kqf) * (kf + kqf)), 0.0f))) * rcp_f(kf + kqf);
     Poles pol{};
-    if (large) {
+    float ur = 0.0f, ui = 0.0f;  // the complex pair
+    if (__builtin_expect(large, 0)) {
         pol = outline_poles((float)s.A, (float)s.B, (float)s.C, (float)x0, (float)y0);
-        eb = fminf(fmaxf(pol.m1, rcp_f(pol.m1)), fmaxf(pol.m2, rcp_f(pol.m2)));
+        const float m1 = sqrt_f(fmaf(pol.r1, pol.r1, pol.i1 * pol.i1)), m2 = sqrt_f(fmaf(pol.r2, pol.r2, pol.i2 * pol.i2));
+        eb = fminf(fmaxf(m1, rcp_f(m1)), fmaxf(m2, rcp_f(fmaxf(m2, 1e-10f))));
+        zero_place(tc, 0.5f * sqrt_f(im2), (float)ca, (float)sa, ur, ui);
     }
     if (!ok || cluster || !(eb > (large ? 1.02f : 1.35f))) return DIRECT_DECLINED;
     GL_STAGE;
@@ -2036,18 +2038,20 @@ GL_HD int direct_arc(const SH& s, double c0l, double c1l, double c2l, double inv
     const float yr = 2.0f * Z * rcp_f(om + sqrt_f(fmaf(om, om, 4.0f * Z * (Z * kk))));
     const float re = eta + sqrt_f(fmaf(eta, eta, 1.0f)), rr = yr + sqrt_f(fmaxf(fmaf(yr, yr, -1.0f), 0.0f));
     float near = fminf(re, rr), exponent = kArcRate;
-    if (large) {
-        float er, ei;
-        pair_place(tc, 0.5f * sqrt_f(im2), (float)cp, (float)sp, er, ei);
-        float ax = images_axis(er, ei, ih, kk);
-        pole_place(pol.r1, pol.i1, (float)cc, (float)sc, er, ei);
-        ax = fminf(ax, images_axis(er, ei, ih, kk));
-        pole_place(pol.r2, pol.i2, (float)cc, (float)sc, er, ei);
-        ax = fmaxf(fminf(ax, images_axis(er, ei, ih, kk)), 1.0f);
+    if (__builtin_expect(large, 0)) {
+        const float zr[3] = {ur, pol.r1, pol.r2}, zi[3] = {ui, pol.i1, pol.i2};
+        float ax = 1e20f;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            float er, ei;
+            pole_place(zr[i], zi[i], (float)cc, (float)sc, er, ei);
+            ax = fminf(ax, images_axis(er, ei, ih, kk));
+        }
+        ax = fmaxf(ax, 1.0f);
         near = fminf(rr, ax + sqrt_f(fmaf(ax, ax, -1.0f)));
         exponent = fmaf(kArcRateK, fmaxf(kf - 0.35f, 0.0f), kArcRate);
         // the contour goes round the star's centre: 2 pi / 3 of the mu integral
-        if (pol.m1 < 1.0f) T.base = fma(c1l * (kTwoPi / 3.0), inv_phi, T.base);
+        if (fmaf(pol.r1, pol.r1, pol.i1 * pol.i1) < 1.0f) T.base = fma(c1l * (kTwoPi / 3.0), inv_phi, T.base);
     }
     const float rate = log_f(near);
     T.k = (double)kk;
@@ -2240,7 +2244,7 @@ GL_HD bool direct_whole(const SH& s, double x0, double y0, DirectWhole& T)
     // the others follow from the roots' sum and product)
     const double im2 = 2.0 * pv * rcp(pp), t2 = -0.5 * b - t, jm2 = fma(-t2, t2, e * rcp(fma(t, t, im2)));
     float d;
-    if (large_or_flat((float)s.k, (float)(s.AC / s.k))) {
+    if (__builtin_expect(large_or_flat((float)s.k, (float)(s.AC / s.k)), 0)) {
         if (!near_map(b, c, e, t, im2, T.kap, d)) return false;
     } else {
         const double tn = fma(t2, t2, 1.0);

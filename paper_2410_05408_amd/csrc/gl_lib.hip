@@ -483,7 +483,11 @@ __global__ void k_snap_nodes(int n, float2* __restrict__ cs)
 //             one arc rule per lane) and whole ellipses (periodic trapezoid);
 //             the few near the inner tangency, whose rules are long, share an
 //             entry between 2 or 4 lanes when there are few of them;
-//   declined  what the direct rules do not fit (about one sample in 10^4);
+//   declined  what the direct rules do not fit (about one sample in 10^4 up to
+//             k = 0.2, up to a tenth above k = 0.5), by the general path, 64 of a
+//             unit's per wavefront (a whole output per wavefront instead, its
+//             sub-samples on as many lanes: 7.6 ms, not 0.54, for 2048 sets of
+//             1000 outputs, k 0.95 to 0.999);
 //   average   each output's sub-samples in order, straight to `out`.
 // Nothing but the inputs and the outputs touches memory.  (The work-list
 // pipeline this replaces ran the same stages as eleven launches over lists in
@@ -560,43 +564,37 @@ __device__ __forceinline__ bool gate(const NetArgs& N, const SH& S, double x0, d
     return true;
 }
 
-// One sub-sample by the general path, for the outputs that hold a sample the
-// direct rules declined (out of line: it needs far more registers and stack
-// than the rest, for one sample in 10^4).
+// One declined sub-sample by the general path, from its centre (a locked set's:
+// cosine and sine of its phase).  Out of line: it needs far more registers and
+// stack than the rest, for one sample in 10^4 up to k = 0.2, and for up to a
+// tenth of them above 0.5.
+struct FluxU {
+    double F;
+    int unconv;
+};
 template <bool CENSUS, int MODE>
-__device__ __attribute__((noinline)) double flux_general(const gl::SetConst& S, double t, int& unconv, int* tally)
+__device__ __attribute__((noinline)) FluxU flux_declined(const gl::SetConst& S, double px, double py, int* tally)
 {
-    double x0, y0;
-    if (!gl::centre_at(S, t, x0, y0)) return 1.0;
-    double d;
     gl::SetConst L;
     const bool lock = MODE == M_ELLIPSOID && S.locked;
-    if (lock) {
-        double sa, ca;
-        gl::phase_at(S, t, false, sa, ca);
-        if (gl::occulted_direct(gl::lock_shape(S, sa, ca), S.c0, S.c1, S.c2, S.inv_phi, x0, y0, d)) return 1.0 - d;
-        gl::lock_at(S, t, L);
-    } else if (gl::occulted_direct(S, S.c0, S.c1, S.c2, S.inv_phi, x0, y0, d)) {
-        return 1.0 - d;  // as (and counted) before
-    }
+    const double x0 = lock ? S.xb * px : px, y0 = lock ? S.d * py : py;
+    if (lock) gl::lock_turned(S, py, px, L);
     const gl::SetConst& s = lock ? L : S;
     if (CENSUS) {
         gl::Census ct;
         int cls = gl::CLS_OUT;
-        d = gl::occulted_hard<gl::Census>(s, x0, y0, &cls, ct);
+        const double d = gl::occulted_hard<gl::Census>(s, x0, y0, &cls, ct);
         tally[cls == gl::CLS_FULL ? 1 : cls == gl::CLS_PARTIAL ? 2 : 3] += 1;
         if (cls == gl::CLS_PARTIAL) tally[9] += 1;
         tally[8] += ct.trap_nodes;
         tally[5] += ct.arcs;
         tally[6] += ct.iters;
         tally[7] += ct.limbs;
-        unconv += ct.unconv;
-        return 1.0 - d;
+        return {1.0 - d, (int)ct.unconv};
     }
     gl::NoCensus nc;
-    d = gl::occulted_hard<gl::NoCensus>(s, x0, y0, nullptr, nc);
-    unconv += nc.unconv;
-    return 1.0 - d;
+    const double d = gl::occulted_hard<gl::NoCensus>(s, x0, y0, nullptr, nc);
+    return {1.0 - d, (int)nc.unconv};
 }
 
 // The sets of CSR blocks: block blk belongs to the set s with off[s] <= blk <
@@ -776,29 +774,22 @@ __device__ __forceinline__ FluxPlace flux_place(const FluxArgs& A, unsigned int 
     return p;
 }
 
-// An output that holds a declined sub-sample, by one wavefront, a sub-sample
-// per lane.  (Listed for a kernel of their own instead, which frees k_flux of
-// the stack that the call to the general path takes: 33 us more on 4096 sets
-// of 3000 x 15 sub-samples, the second kernel being one tail.)
-// gated (surrogate): the gate decides again between planet and sphere; the
-// network's part of an accepted sample is added with the others'.
-template <bool CENSUS, int MODE>
-__device__ __forceinline__ void left_output(const FluxArgs& A, const FluxPlace& pl, int pos, bool gated, int& unconv,
-                                            int* tally)
+// A surrogate batch's output whose network rows found no room, exactly: by one
+// wavefront, a sub-sample per lane.
+__device__ __forceinline__ void exact_output(const FluxArgs& A, const FluxPlace& pl, int pos, int& unconv)
 {
-    const gl::SetConst* S = A.sc + pl.set;
-    const int lane = threadIdx.x & 63, nss = S->n_ss;
-    double F = 0.0;
-    if (lane < nss) {
-        const double t = fma(fma((double)lane + 0.5, 1.0 / (double)nss, -0.5), S->t_exp, pl.times[pos]);
-        if (MODE == M_SURROGATE && gated) {
-            double x0, y0, scale;
-            float feat[gl::kSurFeat];
-            bool on, net;
-            if (flux_centre(A.sc, pl.set, t, x0, y0) && gate(A.net, gate_view(A.sc, pl.set), x0, y0, on, net, feat, scale))
-                S = A.net.sph + pl.set;
+    const gl::SetConst& S = A.sc[pl.set];
+    const int lane = threadIdx.x & 63, nss = S.n_ss;
+    double F = 1.0, x, y, d;
+    if (lane < nss &&
+        flux_centre(A.sc, pl.set, fma(fma((double)lane + 0.5, 1.0 / (double)nss, -0.5), S.t_exp, pl.times[pos]), x, y)) {
+        if (gl::occulted_direct(S, S.c0, S.c1, S.c2, S.inv_phi, x, y, d)) {
+            F = 1.0 - d;
+        } else {
+            const FluxU r = flux_declined<false, M_OBLATE>(S, x, y, nullptr);
+            F = r.F;
+            unconv += r.unconv;
         }
-        F = flux_general<CENSUS, MODE>(*S, t, unconv, tally);
     }
     double sum = 0.0;
     for (int j = 0; j < nss; ++j) sum += __shfl(F, j);
@@ -821,9 +812,9 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
     // in-window outputs of the range, per 128 of them the even ones, then the odd
     __shared__ unsigned long long masks[kFluxMaxRange / 64];
     __shared__ unsigned short win[kFluxMaxRange];             // their offsets in it
-    __shared__ unsigned int left[kFluxMaxRange / 32];  // outputs of the range with a declined sub-sample
     __shared__ int cnt[64];
-    __shared__ int n_wide, n_hard, n_whole, next_tile, any_left;
+    __shared__ unsigned short dec[kUnit];          // entries that the direct rules declined
+    __shared__ int n_wide, n_hard, n_whole, next_tile, n_dec, any_nonet;
     // surrogate: outputs without room for their rows; rows per 64 entries; the unit's first row
     __shared__ unsigned int nonet[MODE == M_SURROGATE ? kFluxMaxRange / 32 : 1];
     __shared__ int net_n[kUnit / 64 + 1];
@@ -846,12 +837,9 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
             t_last = t;
         }
     };
-    if (tid < kFluxMaxRange / 32) {
-        left[tid] = 0u;
-        if (MODE == M_SURROGATE) nonet[tid] = 0u;
-    }
+    if (MODE == M_SURROGATE && tid < kFluxMaxRange / 32) nonet[tid] = 0u;
     unsigned int n_sub = 0u, n_on = 0u, n_acc = 0u;  // surrogate: in window, on the disk, accepted
-    if (tid == 0) any_left = 0;
+    if (tid == 0) any_nonet = 0;
     {
         // window
         const gl::SetConst* sp = A.sc + fresh(si);
@@ -978,7 +966,7 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
             const int tid = fresh_v(threadIdx.x), lane = tid & 63;
             // classify
             if (tid < 64) cnt[tid] = 0;
-            if (tid == 0) next_tile = 0;
+            if (tid == 0) next_tile = n_dec = 0;
             __syncthreads();
             double ts[4];
             int jj[4];
@@ -1140,9 +1128,8 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
                     const int64_t row = at + net_n[k * kFluxWaves + wv] + lanes_below(mn);
                     if (!fits) {
                         // no room: the output is exact, a slot below the end is empty
-                        atomicOr(&left[o >> 5], 1u << (o & 31));
                         atomicOr(&nonet[o >> 5], 1u << (o & 31));
-                        any_left = 1;
+                        any_nonet = 1;
                         if (row < A.net.cap) {
                             A.net.slot[row] = -1;
                             for (int i = 0; i < gl::kSurFeat; ++i) A.net.x[row * gl::kSurFeat + i] = 0;
@@ -1238,13 +1225,10 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
                         } else if (CENSUS && g == 0) {
                             tally[3] += 1;
                         }
+                        // (a declined sample keeps its centre)
                         if (g == 0) {
-                            fx[e] = F;
-                            if (!ok) {
-                                const int o = win[o0 + (int)(((float)e + 0.5f) * inv_nss_f)];
-                                atomicOr(&left[o >> 5], 1u << (o & 31));
-                                any_left = 1;
-                            }
+                            if (ok) fx[e] = F;
+                            else dec[atomicAdd(&n_dec, 1)] = (unsigned short)v0;
                         }
                     }
                     lap(C_ARCS);
@@ -1264,25 +1248,35 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
                 }
             }
             __syncthreads();
+            if (const int nd = __builtin_amdgcn_readfirstlane(n_dec); __builtin_expect(nd, 0)) {
+                // declined
+                for (int i = fresh_v(threadIdx.x); i < nd; i += kFluxThreads) {
+                    const int v = dec[i], e = v & 1023;
+                    const gl::SetConst* s = (MODE == M_SURROGATE && (v & 0x8000) ? A.net.sph : A.sc) + si;
+                    const FluxU r = flux_declined<CENSUS, MODE>(*s, fx[e], fy[e], tally);
+                    fx[e] = r.F;
+                    unconv += r.unconv;
+                }
+                __syncthreads();
+                lap(C_DECLINED);
+            }
             __builtin_amdgcn_s_setprio(kPrioLatency);
             // average
             for (int o = fresh_v(threadIdx.x); o < no; o += kFluxThreads) {
                 double sum = 0.0;
                 for (int j = 0; j < nss; ++j) sum += fx[o * nss + j];
                 const int w = win[o0 + o];
-                if (!((left[w >> 5] >> (w & 31)) & 1u)) out[w] = sum / (double)nss;
+                if (MODE != M_SURROGATE || !((nonet[w >> 5] >> (w & 31)) & 1u)) out[w] = sum / (double)nss;
             }
             __syncthreads();
             lap(C_AVERAGE);
         }
     }
-    if (__builtin_amdgcn_readfirstlane(any_left)) {
+    if (MODE == M_SURROGATE && __builtin_amdgcn_readfirstlane(any_nonet)) {
         int turn = 0;
         for (int w = 0; w < kFluxMaxRange / 32; ++w)
-            for (unsigned int bits = __builtin_amdgcn_readfirstlane(left[w]); bits; bits &= bits - 1u)
-                if ((turn++ & (kFluxWaves - 1)) == wv)
-                    left_output<CENSUS, MODE>(A, pl, 32 * w + __builtin_ctz(bits),
-                                              !(MODE == M_SURROGATE && (nonet[w] & bits & (0u - bits))), unconv, tally);
+            for (unsigned int bits = __builtin_amdgcn_readfirstlane(nonet[w]); bits; bits &= bits - 1u)
+                if ((turn++ & (kFluxWaves - 1)) == wv) exact_output(A, pl, 32 * w + __builtin_ctz(bits), unconv);
         lap(C_DECLINED);
     }
     if (CENSUS)
