@@ -481,8 +481,8 @@ __global__ void k_snap_nodes(int n, float2* __restrict__ cs)
 //   evaluate  tiles of 64 sorted entries, handed out by an LDS counter, the
 //             long ones first: crossing ellipses (quartic, closed forms and
 //             one arc rule per lane) and whole ellipses (periodic trapezoid);
-//             the few near the inner tangency, whose rules are long, share an
-//             entry between 2 or 4 lanes when there are few of them;
+//             those near the inner tangency, whose rules are long, share an
+//             entry between 4 lanes;
 //   declined  what the direct rules do not fit (about one sample in 10^4 up to
 //             k = 0.2, up to a tenth above k = 0.5), by the general path, 64 of a
 //             unit's per wavefront (a whole output per wavefront instead, its
@@ -506,18 +506,25 @@ static_assert(kFluxMaxRange <= 64 * 128 && kFluxMaxRange % kWinRound == 0, "128 
 // two neighbouring outputs: times and fluxes are 8-byte aligned (a 16-byte
 // access needs 4 here)
 typedef double pair2 __attribute__((ext_vector_type(2), aligned(8)));
-// sort buckets, longest first: crossing ellipses with an arc beyond ~145
-// degrees either side or none (near the inner tangency), those with shorter
-// arcs in four steps, then whole ellipses by falling trapezoid order (the
-// longest few together: 32 buckets, five bits)
+// sort buckets, longest first: ellipses near the inner tangency with no
+// crossing in sight, crossing ones in four steps of their arc's length, then
+// whole ellipses by falling trapezoid order (the longest few together: 32
+// buckets, five bits)
 constexpr int kBWide = 0, kBHard = 1, kBWhole = 5;
 constexpr int kFluxBuckets = 32;
 constexpr int kBTop = kFluxBuckets - kBWhole + 3;  // half orders from here on share a bucket
+// Lanes per entry of the first bucket, whose rules are the longest: always the
+// same number, so that a sample's bits do not depend on how many others its
+// unit holds.  All lanes of an entry set it up, so it has to be the few with
+// long rules: with arcs beyond 145 degrees among them (key < -0.82) 2048 own
+// grids take 1016 us, 904 with the limit at -1; one lane when they are many, up
+// to 4 when they are few: 922, and 48 sets of 1009 x 3 34.6, not 23.5.
+constexpr int kWideLanes = 4;
 
 __device__ __forceinline__ int flux_bucket(int cls, float key)
 {
     if (cls >= 0) return kBWhole + kBTop - std::min(cls, kBTop);
-    return key < -0.82f ? kBWide : key < -0.5f ? kBHard : key < 0.0f ? kBHard + 1 : key < 0.5f ? kBHard + 2 : kBHard + 3;
+    return key < -1.0f ? kBWide : key < -0.5f ? kBHard : key < 0.0f ? kBHard + 1 : key < 0.5f ? kBHard + 2 : kBHard + 3;
 }
 
 // Issue priority of the stages that wait for memory, LDS and each other (window,
@@ -1157,7 +1164,7 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
             __builtin_amdgcn_s_setprio(0);
             const int cw = __builtin_amdgcn_readfirstlane(n_wide), ch = __builtin_amdgcn_readfirstlane(n_hard),
                       ct = __builtin_amdgcn_readfirstlane(n_whole);
-            const int tw = (cw + 63) >> 6, th = (ch + 63) >> 6, tt = (ct + 63) >> 6;
+            const int tw = (cw + 63 / kWideLanes) / (64 / kWideLanes), pw = (cw + 63) & ~63, th = (ch + 63) >> 6, tt = (ct + 63) >> 6;
             for (;;) {
                 int tile = 0;
                 const int lane = fresh_v(threadIdx.x) & 63;
@@ -1180,15 +1187,15 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
                 if (tile < tw + th) {
                     // crossing ellipses: G lanes per entry
                     const bool wide = tile < tw;
-                    const int G = wide && cw <= 16 ? 4 : wide && cw <= 32 ? 2 : 1;
+                    const int G = wide ? kWideLanes : 1;
                     const int g = lane & (G - 1);
-                    const int i = (G == 1 ? lane : G == 2 ? lane >> 1 : lane >> 2) + ((wide ? tile : tile - tw) << 6);
+                    const int i = wide ? (64 * tile + lane) / kWideLanes : 64 * (tile - tw) + lane;
                     auto reduce = [&](double v) {
                         for (int d = 1; d < G; d <<= 1) v += __shfl_xor(v, d);
                         return v;
                     };
                     if (i < (wide ? cw : ch)) {
-                        const int v0 = ord[i + (wide ? 0 : tw << 6)], e = v0 & 1023;
+                        const int v0 = ord[i + (wide ? 0 : pw)], e = v0 & 1023;
                         double x0, y0;
                         const gl::Shape sh = entry(v0, x0, y0);
                         gl::DirectArc T;
@@ -1235,7 +1242,7 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
                 } else {
                     const int i = lane + ((tile - tw - th) << 6);
                     if (i < ct) {
-                        const int v = ord[i + ((tw + th) << 6)], e = v & 1023, h = ((v >> 10) & 31) + 1;
+                        const int v = ord[i + pw + (th << 6)], e = v & 1023, h = ((v >> 10) & 31) + 1;
                         double x0, y0;
                         const gl::Shape sh = entry(v, x0, y0);
                         fx[e] = 1.0 - gl::direct_whole_delta(sh, S.c0, S.c1, S.c2, S.inv_phi, x0, y0, gl::whole_lin(sh, x0, y0, h));

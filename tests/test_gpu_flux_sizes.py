@@ -171,3 +171,21 @@ def test_own_grids_by_number_of_sets(gpu_lib, ctx, oracle, n_sets):
     got = flux(gpu_lib, ctx, w)
     ref = oracle.flux_batch(w.params, w.times, offsets=w.offsets, n_ss=w.n_ss, t_exp=w.t_exp)
     assert np.abs(got - ref.reshape(-1)).max() <= TOL
+
+
+def test_bits_of_a_sample_alone(gpu_lib, ctx):
+    # long arcs (near the inner tangency) by the hundred in a unit, and each one
+    # the only output of a set: 1 and 4 lanes per sample, the same bits
+    from paper_2410_05408_amd import workloads as W
+    print("case: 4 sets of 900 grazing outputs, together and one by one", flush=True)
+    rng = np.random.default_rng(29)
+    p = W.walker_batch(n_sets=4).params
+    p[W.K], p[W.F], p[W.T0] = [0.06, 0.1, 0.12, 0.3], [0.1, 0.0, 0.3, 0.2], 0.0
+    p[W.B] = 1.0 - 0.97 * p[W.K]
+    t = rng.uniform(-0.06, 0.06, 900)
+    one = np.ones(4, np.int32)
+    got = flux(gpu_lib, ctx, W.Workload("together", np.ascontiguousarray(p), t, None, one, np.zeros(4), {})).reshape(4, -1)
+    n = 4 * t.size
+    alone = W.Workload("alone", np.ascontiguousarray(np.repeat(p, t.size, axis=1)), np.tile(t, 4),
+                       np.arange(n + 1, dtype=np.int64), np.ones(n, np.int32), np.zeros(n), {})
+    assert np.array_equal(got, flux(gpu_lib, ctx, alone).reshape(4, -1))
