@@ -496,8 +496,14 @@ gl_status gl_surrogate_file_read(const char *path, gl_surrogate_config *cfg, flo
  * scale * network(features), or the sphere alone where the bin takes it.
  * Every other sub-sample is computed exactly.
  * Outputs are box-averaged in order.  The network's rows wait in memory of the
- * context, sized from what earlier batches asked for; outputs without room
- * there are computed exactly.  Asynchronous unless a count is
+ * context: room for 16 per output up to 2^24 rows (a quarter per output where
+ * that is more), and for what an earlier batch's pass asked for and a quarter more, within
+ * an eighth of the device's memory.  Within it a batch's values are
+ * reproducible bit for bit.  Where a pass asks for more, the outputs without
+ * room are computed exactly instead; which ones they are depends on the order in
+ * which workgroups run and on what earlier batches of the context asked for, so
+ * such values can differ between calls by what the gate tolerates.
+ * Asynchronous unless a count is
  * requested: *n_sub_out and *n_fallback_out (host, may be NULL) then receive,
  * after waiting for `stream`, the in-window sub-samples and those of them
  * whose ellipse reaches the disk but that the gate rejected. */

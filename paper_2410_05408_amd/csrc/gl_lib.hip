@@ -30,6 +30,7 @@
 #include "gl_device.h"
 #include "gl_index.h"
 #include "gl_internal.h"
+#include "gl_room.h"
 
 namespace {
 
@@ -1668,18 +1669,12 @@ void free_net(gl_ctx* ctx)
     N = NetArgs{};
 }
 
-// Room for the network's rows: for a batch of n_out outputs at first 16 rows
-// per output, at most the larger of a million and a quarter row per output
-// (52 bytes each); then what the passes so far have asked for and a quarter
-// more, within an eighth of the device's memory.  Units that find no room are
+// Room for the network's rows (gl::net_rows).  Units that find none are
 // evaluated exactly.
 gl_status ensure_net(gl_ctx* ctx, int64_t n_out)
 {
-    constexpr int64_t kRow = sizeof(uint16_t) * gl::kSurFeat + sizeof(int64_t) + sizeof(double) + sizeof(float);
-    int64_t want = std::min(16 * n_out, std::max<int64_t>((int64_t)1 << 20, n_out / 4));
-    const int64_t seen = (int64_t) * (const volatile unsigned long long*)ctx->rows;
-    if (seen > ctx->net.cap) want = std::max(want, seen + seen / 4);
-    want = std::min(want, ctx->mem_total / 8 / kRow);
+    static_assert(gl::kNetRowBytes == sizeof(uint16_t) * gl::kSurFeat + sizeof(int64_t) + sizeof(double) + sizeof(float), "a row");
+    const int64_t want = gl::net_rows(n_out, (int64_t) * (const volatile unsigned long long*)ctx->rows, ctx->net.cap, ctx->mem_total);
     if (want <= ctx->net.cap) return GL_OK;
     drop_graph(ctx);
     GL_HIP(hipDeviceSynchronize(), "hipDeviceSynchronize");

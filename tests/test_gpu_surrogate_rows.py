@@ -57,3 +57,26 @@ def test_rows_complete(gpu_lib, tmp_path, n_sets, n_times, n_ss):
         assert np.any(np.abs(first - exact) <= 64 * 2.3e-16 * 2)
     else:
         assert np.array_equal(first, again)
+
+
+def test_first_batch_of_two_million_rows(gpu_lib, tmp_path):
+    # every sub-sample a network row, 15 per output: the first batch on a context
+    # has room for all of them
+    import torch
+    from paper_2410_05408_amd import workloads as W
+    gl = gpu_lib
+    n_sets, n_times, n_ss = 70, 2000, 15
+    print(f"case: {n_sets} sets of {n_times} outputs of {n_ss} sub-samples", flush=True)
+    p = W.walker_batch(n_sets=n_sets).params
+    p[W.B], p[W.T0] = 0.3, 0.0
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    ctx = gl.Context(0)
+    sur = _surrogate(gl, ctx, str(tmp_path / "s.bin"))
+    d = {"params": dev(p), "times": dev(np.linspace(-0.05, 0.06, n_times)), "offsets": None,
+         "n_ss": dev(np.full(n_sets, n_ss, np.int32)), "t_exp": dev(np.full(n_sets, 1e-3))}
+    outs = []
+    for _ in range(2):
+        out = torch.empty(n_sets * n_times, dtype=torch.float64, device="cuda")
+        assert sur.lightcurve(d, out, tol=1e-6) == (n_sets * n_times * n_ss, 0)
+        outs.append(out)
+    assert torch.equal(outs[0], outs[1])
