@@ -1350,6 +1350,7 @@ struct gl_ctx {
     gl::SetConst* sc = nullptr;
     gl::SetConst* sc_sph = nullptr;  // equal-area spheres (surrogate batches)
     NetArgs net{};                   // rows of the network (surrogate batches)
+    bool net_full = false;           // no memory for more of them
     unsigned long long* rows = nullptr;      // the most rows a pass asked for (pinned host memory)
     unsigned long long* rows_dev = nullptr;
     int64_t* seg_begin = nullptr;
@@ -1670,21 +1671,31 @@ void free_net(gl_ctx* ctx)
 }
 
 // Room for the network's rows (gl::net_rows).  Units that find none are
-// evaluated exactly.
+// evaluated exactly; so a context that has some goes on with it where no more
+// can be had, and does not ask again.
 gl_status ensure_net(gl_ctx* ctx, int64_t n_out)
 {
     static_assert(gl::kNetRowBytes == sizeof(uint16_t) * gl::kSurFeat + sizeof(int64_t) + sizeof(double) + sizeof(float), "a row");
-    const int64_t want = gl::net_rows(n_out, (int64_t) * (const volatile unsigned long long*)ctx->rows, ctx->net.cap, ctx->mem_total);
-    if (want <= ctx->net.cap) return GL_OK;
+    NetArgs& N = ctx->net;
+    const int64_t want = gl::net_rows(n_out, (int64_t) * (const volatile unsigned long long*)ctx->rows, N.cap, ctx->mem_total);
+    if (want <= N.cap || (ctx->net_full && N.cap > 0)) return GL_OK;
     drop_graph(ctx);
     GL_HIP(hipDeviceSynchronize(), "hipDeviceSynchronize");
-    free_net(ctx);
-    NetArgs& N = ctx->net;
-    if (hipMalloc(&N.x, sizeof(uint16_t) * gl::kSurFeat * want) != hipSuccess ||
-        hipMalloc(&N.slot, sizeof(int64_t) * want) != hipSuccess ||
-        hipMalloc(&N.scale, sizeof(double) * want) != hipSuccess || hipMalloc(&N.y, sizeof(float) * want) != hipSuccess) {
-        free_net(ctx);
-        return fail(ctx, GL_ERR_NOMEM, "network rows");
+    void** const slots[] = {(void**)&N.x, (void**)&N.slot, (void**)&N.scale, (void**)&N.y};
+    const int64_t bytes[] = {(int64_t)sizeof(uint16_t) * gl::kSurFeat * want, (int64_t)sizeof(int64_t) * want,
+                             (int64_t)sizeof(double) * want, (int64_t)sizeof(float) * want};
+    const bool ok = gl::replace_all(
+        slots, bytes,
+        [](int64_t n) {
+            void* p = nullptr;
+            return hipMalloc(&p, (size_t)n) == hipSuccess ? p : nullptr;
+        },
+        [](void* p) { (void)hipFree(p); });
+    if (!ok) {
+        (void)hipGetLastError();
+        if (N.cap == 0) return fail(ctx, GL_ERR_NOMEM, "network rows");
+        ctx->net_full = true;
+        return GL_OK;
     }
     N.cap = want;
     return GL_OK;

@@ -23,4 +23,24 @@ inline int64_t net_rows(int64_t n_out, int64_t seen, int64_t cap, int64_t mem_to
     return want < most ? want : most;
 }
 
+// New buffers of the given sizes for all of `slots`, or none: where one cannot
+// be had, the old ones stay.
+template <int N, class Alloc, class Free>
+bool replace_all(void** const (&slots)[N], const int64_t (&bytes)[N], Alloc&& alloc, Free&& release)
+{
+    void* fresh[N] = {};
+    for (int i = 0; i < N; ++i) {
+        fresh[i] = alloc(bytes[i]);
+        if (!fresh[i]) {
+            for (int j = 0; j < i; ++j) release(fresh[j]);
+            return false;
+        }
+    }
+    for (int i = 0; i < N; ++i) {
+        if (*slots[i]) release(*slots[i]);
+        *slots[i] = fresh[i];
+    }
+    return true;
+}
+
 }  // namespace gl

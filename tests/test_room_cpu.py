@@ -35,3 +35,14 @@ def test_rows_follow_the_demand(check):
     assert int(check("rows", 300, 4000, 4800, MEM)) == 4800
     assert int(check("rows", 1 << 26, 1 << 40, 1 << 24, MEM)) == MEM // 8 // 52
     assert int(check("rows", 1 << 26, 0, 0, 1 << 30)) == (1 << 30) // 8 // 52
+
+
+@pytest.mark.parametrize("held", [0, 1])
+@pytest.mark.parametrize("fail_at", [0, 1, 2, 9])
+def test_rows_stay_where_no_more_can_be_had(check, held, fail_at):
+    ok, good, kept, there, live = map(int, check("replace", held, fail_at).split())
+    assert good
+    if fail_at == 9:
+        assert (ok, kept, there, live) == (1, 0, 3, 3)
+    else:
+        assert (ok, kept, there, live) == (0, 3, 3 * held, 3 * held)
