@@ -139,7 +139,8 @@ STAGE_KERNELS = {"window": "k_flux (window)", "classify": "k_flux (classificatio
                  "trapezoid": "k_flux (whole ellipses)", "hard": "k_flux (crossing ellipses' set-up)",
                  "nested": "k_flux (general path)", "arcs": "k_flux (arc rule)", "combine": "k_flux (averages)"}
 # FP64 operations of one evaluation of the arc rule at its mean order of 12
-# intervals: five pairs of nodes of 60 and the centre node
+# intervals: five pairs of nodes of 60 and the centre node (gl_flop_model rates
+# the item as a 21-node Gauss-Kronrod piece, which only the general path's are)
 ARC_RULE_FLOP = 5 * 60 + 30
 # stages whose work is FP64 arithmetic (the others move data)
 FLOP_STAGES = ("classify", "trapezoid", "hard", "nested", "arcs")
@@ -248,10 +249,9 @@ def oracle_sample(w, got, n_sets=4, n_changed=2000, seed=0):
     return {"outputs_compared": int(sel.size), "max_abs_err": float(np.max(np.abs(flat[sel] - ref)))}
 
 
-def exact_leg(gl, w, steps, warmup, trials=10, autotune=False, check_oracle=True, dev="cuda:0"):
+def exact_leg(gl, w, steps, warmup, trials=10, check_oracle=True, dev="cuda:0"):
     """One workload through gl_lightcurve_batch on its own context: warm-up
-    (the first batch sizes the workspace), optional
-    autotuning before the graph is captured, `steps` graph-replayed steps
+    (the first batch sizes the workspace), `steps` graph-replayed steps
     bracketed by synchronisations, `trials` single steps timed by HIP events
     on the launch stream (median), a stage-timing pass, the work census, and
     the rooflines of its stages."""
@@ -267,16 +267,13 @@ def exact_leg(gl, w, steps, warmup, trials=10, autotune=False, check_oracle=True
 
     step()  # sizes the workspace
     stream.synchronize()
-    if autotune:
-        log(f"  autotune on {w.name}")
-        gl.gl_autotune(ctx.handle, d["params"], d["times"], out, stream=stream, **args)
     for _ in range(warmup):
         step()
     stream.synchronize()
     torch.cuda.synchronize()
     if gl.gl_ctx_sync_status(ctx.handle) != gl.GL_OK:
         raise RuntimeError(gl.gl_ctx_last_error(ctx.handle))
-    fused, passes = gl.gl_ctx_get_overflow(ctx.handle)
+    _, passes = gl.gl_ctx_get_overflow(ctx.handle)
 
     log(f"  timed region: {steps} steps (graph replay)")
     torch.cuda.synchronize()
@@ -325,9 +322,7 @@ def exact_leg(gl, w, steps, warmup, trials=10, autotune=False, check_oracle=True
         "in_transit_points": in_transit, "outputs": w.n_out, "sub_samples": w.n_sub,
         "roofline": roof, "roofline_stages": roof_stages, "stage_ms": stage_ms,
         "pipeline_ms_timed_direct": pipe_ms,
-        "plan": {"waves_per_cu": gl.gl_ctx_get_plan(ctx.handle),
-                 "stage_plan_classify_hard_trap_arcs": list(gl.gl_ctx_get_stage_plan(ctx.handle)), "passes": passes,
-                 "fused_chunks": fused, "autotuned": autotune},
+        "passes": passes,
         "census": census, "unconverged_arcs": unconv,
     }
     if check_oracle:
@@ -408,8 +403,7 @@ def timed_steps(step, stream, steps, warmup, trials=10):
 
 def ellipsoid_leg(gl, workloads, steps, warmup, dev="cuda:0"):
     """General and tidally-locked triaxial planets (gl_lightcurve_batch_ellipsoid):
-    the mixed batch, and its free and locked halves on their own (locked sets
-    take the fused per-sample path), each with its own autotuned plan."""
+    the mixed batch, and its free and locked halves on their own."""
     import torch
     res = {}
     w = workloads.ellipsoid_batch()
@@ -433,8 +427,6 @@ def ellipsoid_leg(gl, workloads, steps, warmup, dev="cuda:0"):
             gl.gl_lightcurve_batch_ellipsoid(ctx.handle, p, td, out, offsets=od, n_ss=ss, t_exp=te, stream=stream)
 
         step()  # sizes the workspace
-        gl.gl_autotune_ellipsoid(ctx.handle, p, td, out, offsets=od, n_ss=ss, t_exp=te, stream=stream)
-        plan = gl.gl_ctx_get_stage_plan(ctx.handle)
         ms, med = timed_steps(step, stream, steps, warmup)
         if gl.gl_ctx_sync_status(ctx.handle) != gl.GL_OK:
             raise RuntimeError(gl.gl_ctx_last_error(ctx.handle))
@@ -442,8 +434,7 @@ def ellipsoid_leg(gl, workloads, steps, warmup, dev="cuda:0"):
         n_sub = int(np.sum(seg * w.n_ss[idx]))
         res[name] = {"n_sets": int(idx.size), "outputs": int(times.size), "sub_samples": n_sub,
                      "in_transit_points": int(np.sum(got < 1.0)), "ms_per_step": ms, "ms_median_event": med,
-                     "points_per_s": times.size / (ms * 1e-3), "sub_samples_per_s": n_sub / (ms * 1e-3),
-                     "stage_plan_classify_hard_trap_arcs": list(plan)}
+                     "points_per_s": times.size / (ms * 1e-3), "sub_samples_per_s": n_sub / (ms * 1e-3)}
     res["unconverged_arcs"] = gl.gl_ctx_get_unconverged(ctx.handle)
     ctx.close()
     return res
@@ -473,12 +464,8 @@ def mcmc_leg(gl, workloads, steps, warmup, n_walkers=4096, dev="cuda:0"):
     params = torch.empty((10, n_walkers), dtype=torch.float64, device=dev)
     ctx = gl.Context(0)
     stream = torch.cuda.Stream()
-    # the stage plan tuned on the walkers' own light curves (the likelihood
-    # batch runs the same kernels, then the reduction)
     gl.gl_walkers_to_params(wd, params)
     torch.cuda.synchronize()
-    gl.gl_autotune(ctx.handle, params, td, model, n_ss=ss, t_exp=te, stream=stream)
-    plan = gl.gl_ctx_get_stage_plan(ctx.handle)
 
     def step():
         gl.gl_loglike_batch(ctx.handle, wd, td, dd, sd, model, chi2, ll, n_ss=ss, t_exp=te, stream=stream)
@@ -487,7 +474,6 @@ def mcmc_leg(gl, workloads, steps, warmup, n_walkers=4096, dev="cuda:0"):
     if gl.gl_ctx_sync_status(ctx.handle) != gl.GL_OK:
         raise RuntimeError(gl.gl_ctx_last_error(ctx.handle))
     ctx2 = gl.Context(0)
-    gl.gl_ctx_set_stage_plan(ctx2.handle, *plan)
 
     def lc():
         gl.gl_lightcurve_batch(ctx2.handle, params, td, model, n_ss=ss, t_exp=te, stream=stream)
@@ -507,7 +493,6 @@ def mcmc_leg(gl, workloads, steps, warmup, n_walkers=4096, dev="cuda:0"):
         "config": {"workload": "jwst_visit_walker_ball", "n_walkers": n_walkers, "n_times": int(t.size),
                    "n_ss": n_ss, "cadence_min": 2.0, "sigma_ppm": 20.0},
         "ms_per_step": ms, "ms_median_event": med,
-        "stage_plan_classify_hard_trap_arcs": list(plan),
         "walker_evaluations_per_s": n_walkers / (ms * 1e-3),
         "points_per_s": n_walkers * t.size / (ms * 1e-3),
         "lightcurve_only_ms_median_event": med_lc,
@@ -558,14 +543,13 @@ def main():
     if args.only and args.only != "walker_batch":
         w = workloads.by_name(args.only)
         log(f"{args.only}: {w.n_out} outputs")
-        res, _ = exact_leg(gl, w, args.steps, args.warmup, autotune=args.only == "uneven_batch",
-                           check_oracle=False)
+        res, _ = exact_leg(gl, w, args.steps, args.warmup, check_oracle=False)
         print(json.dumps({"workload": args.only, **res}), flush=True)
         return
 
     log("walker batch (4096 sets x 3000 shared times x 15 sub-samples)")
     w = workloads.walker_batch()
-    head, got = exact_leg(gl, w, args.steps, args.warmup, autotune=True, check_oracle=False)
+    head, got = exact_leg(gl, w, args.steps, args.warmup, check_oracle=False)
     res = {
         "metric": "light-curve points/sec on 1 MI355X: exact (≤1e-9) vs surrogate+fallback (≤1 ppm)",
         "value": head.pop("value"),
@@ -588,11 +572,11 @@ def main():
     if not args.no_extra_configs and not args.only:
         res["configs"] = {}
         log("high-cadence batch (512 sets x 65536 shared times, no supersampling)")
-        hc, _ = exact_leg(gl, workloads.high_cadence(), args.steps, args.warmup, autotune=True)
+        hc, _ = exact_leg(gl, workloads.high_cadence(), args.steps, args.warmup)
         res["configs"]["high_cadence"] = {"config": {"n_sets": 512, "n_times": 65536, "n_ss": 1,
                                                      "cadence_s": 60, "seed": 3}, **hc}
         log("uneven CSR batch (16384 walkers, own grids of 200..20000 times, n_ss in {1,5,15})")
-        ub, _ = exact_leg(gl, workloads.uneven_batch(), max(3, args.steps // 4), args.warmup, autotune=True)
+        ub, _ = exact_leg(gl, workloads.uneven_batch(), max(3, args.steps // 4), args.warmup)
         res["configs"]["uneven_batch"] = {"config": {"n_sets": 16384, "grid_len": "log-uniform [200, 20000]",
                                                      "n_ss": "{1, 5, 15}", "layout": "CSR", "seed": 4}, **ub}
         torch.cuda.synchronize()
@@ -610,8 +594,6 @@ def main():
         d = gl.to_device(w, "cuda:0")
         exact_out = torch.from_numpy(got).to("cuda:0")
         ctx = gl.Context(0)
-        # the exact leg's tuned plan (the gated batch runs the same kernels)
-        gl.gl_ctx_set_stage_plan(ctx.handle, *res["plan"]["stage_plan_classify_hard_trap_arcs"])
         res["surrogate"] = surrogate_leg(ctx, d, exact_out, res["ms_per_step"], w.n_out, args)
         ctx.close()
     if not args.no_cpu_baseline and not args.only:

@@ -29,7 +29,7 @@ FLAGS = [
 
 def build(verbose: bool = False, out: str = LIB, defines=()) -> str:
     """Compiles the library to ``out``; ``defines`` are extra -D macros
-    (e.g. GL_COMPUTE_WAVES_PER_EU=4)."""
+    (e.g. GL_ARC_TOL=1e-7)."""
     srcs = [os.path.join(CSRC, "gl_lib.hip"), os.path.join(CSRC, "gl_mlp.hip"),
             os.path.join(CSRC, "gl_mcmc.hip"), os.path.join(CSRC, "gl_io.cpp")]
     cmd = [HIPCC, *FLAGS, *[f"-D{d}" for d in defines], "-I", os.path.join(ROOT, "include"),

@@ -50,7 +50,7 @@ struct alignas(128) LineCount {
 };
 
 struct Counters {
-    unsigned long long total_chunks;  // written by k_scan (workgroups or chunks)
+    unsigned long long total_chunks;  // own grids: workgroups or chunks (k_prep, k_scan)
     unsigned int status;              // bit 0: invalid set, bit 1: bad CSR segment, bit 2: non-finite time
     unsigned int pad;
     // arcs accepted at the arc rule's last level above its tolerance, summed
@@ -169,8 +169,11 @@ __global__ void k_prep(const double* __restrict__ params, int64_t ld, int64_t n_
         if (flag) atomicOr(&ctr->status, flag);
         sc[s] = c;
         if (sph) sph[s] = gl::sphere_of(c);
-        seg_begin[s] = b;
-        seg_len[s] = e - b;
+        // (the fused pass takes a shared grid's places from the set's number)
+        if (offsets || !fused_range) {
+            seg_begin[s] = b;
+            seg_len[s] = e - b;
+        }
         if (cps_shared > 0) {
             // shared grid, every set has cps_shared chunks: the exclusive scan in
             // closed form (no k_scan launch)
@@ -179,7 +182,7 @@ __global__ void k_prep(const double* __restrict__ params, int64_t ld, int64_t n_
                 chunk_off[n_sets] = n_sets * cps_shared;
                 ctr->total_chunks = (unsigned long long)(n_sets * cps_shared);
             }
-        } else {
+        } else if (offsets) {
             const int64_t per = fused_range ? flux_range_of(most_of(fused_range, s, n_sets), ok ? nss : 1) : kChunk;
             count = (e - b + per - 1) / per;
             if (!scan_most) chunk_off[s] = count;
@@ -1629,7 +1632,7 @@ gl_status enqueue_flux(gl_ctx* ctx, const Batch& b)
     A.row = gl::flux_row(grid);
     hipLaunchKernelGGL(prep, dim3(prep_blocks), dim3(prep_threads), 0, st, b.params, b.ld, b.n_sets, b.offsets, b.n_times,
                        b.n_ss, b.t_exp, ctx->sc, ctx->seg_begin, ctx->seg_len, ctx->chunk_off, ctx->ctr,
-                       shared ? (int64_t)1 : (int64_t)0, b.first, b.last, b.net ? ctx->sc_sph : nullptr, b.sigma, b.n_times,
+                       (int64_t)0, b.first, b.last, b.net ? ctx->sc_sph : nullptr, b.sigma, b.n_times,
                        norm ? &ctx->ctr->ll_norm : nullptr, (int)b.range, scan_here ? grid : (int64_t)0,
                        b.first && (CENSUS || ev || b.net));
     if (!shared) {
@@ -1735,10 +1738,8 @@ gl_status run_batch(gl_ctx* ctx, const Batch& b, bool census)
         q.t_exp = b.t_exp ? b.t_exp + a : nullptr;
         if (b.offsets) {
             q.offsets = b.offsets + a;
-            q.max_chunks = b.n_times / kChunk + q.n_sets;
         } else {
             q.out = b.out + a * b.n_times;
-            q.max_chunks = (b.n_times + kChunk - 1) / kChunk * q.n_sets;
         }
         q.first = p == 0;
         q.last = p == T - 1;

@@ -656,7 +656,7 @@ k_mlp_infer(const bf16* __restrict__ X, int64_t n_cap, const unsigned long long*
     __shared__ __align__(16) bf16 Wl[2][kPiece];
     __shared__ __align__(16) float bl[DEPTH][W];
     __shared__ __align__(16) float w4[W];
-    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, lg = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int64_t n = n_cap;
     if (n_dev) n = min(n, (int64_t)*n_dev);
