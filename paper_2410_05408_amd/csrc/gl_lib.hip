@@ -510,8 +510,8 @@ static_assert(kFluxMaxRange <= 64 * 128 && kFluxMaxRange % kWinRound == 0, "128 
 // two neighbouring outputs: times and fluxes are 8-byte aligned (a 16-byte
 // access needs 4 here)
 typedef double pair2 __attribute__((ext_vector_type(2), aligned(8)));
-// sort buckets, longest first: ellipses near the inner tangency with no
-// crossing in sight, crossing ones in four steps of their arc's length, then
+// sort buckets, longest first: ellipses near the inner tangency (an arc beyond
+// ~172 degrees either side or none), crossing ones in four steps of their arc's length, then
 // whole ellipses by falling trapezoid order (the longest few together: 32
 // buckets, five bits)
 constexpr int kBWide = 0, kBHard = 1, kBWhole = 5;
@@ -520,15 +520,16 @@ constexpr int kBTop = kFluxBuckets - kBWhole + 3;  // half orders from here on s
 // Lanes per entry of the first bucket, whose rules are the longest: always the
 // same number, so that a sample's bits do not depend on how many others its
 // unit holds.  All lanes of an entry set it up, so it has to be the few with
-// long rules: with arcs beyond 145 degrees among them (key < -0.82) 2048 own
-// grids take 1016 us, 904 with the limit at -1; one lane when they are many, up
-// to 4 when they are few: 922, and 48 sets of 1009 x 3 34.6, not 23.5.
+// long rules: with the limit on the arc at cos(delta) = -0.82 2048 own grids take 1016 us,
+// 945 at -0.98, 934 at -0.99 and 926 at -1; 64 walkers of 1009 x 3 32.5 at -0.98, 31.6
+// at -0.99 and 35.3 at -1.  (One lane when they are many, up to 4 when they
+// are few, by the unit: 938 and 32.7, and 48 sets of 1009 x 3 34.6, not 23.5.)
 constexpr int kWideLanes = 4;
 
 __device__ __forceinline__ int flux_bucket(int cls, float key)
 {
     if (cls >= 0) return kBWhole + kBTop - std::min(cls, kBTop);
-    return key < -1.0f ? kBWide : key < -0.5f ? kBHard : key < 0.0f ? kBHard + 1 : key < 0.5f ? kBHard + 2 : kBHard + 3;
+    return key < -0.99f ? kBWide : key < -0.5f ? kBHard : key < 0.0f ? kBHard + 1 : key < 0.5f ? kBHard + 2 : kBHard + 3;
 }
 
 // Issue priority of the stages that wait for memory, LDS and each other (window,
