@@ -1671,7 +1671,7 @@ GL_HD Shape lock_shape(const LK& L, double sa, double ca)
 
 // Whole-ellipse rules: an n-node trapezoid errs like exp(-n d), d the distance
 // of the nearest complex zero of 1 - r^2 from the real axis.
-constexpr float kWholeRate = 23.5f;
+constexpr float kWholeRate = 24.0f;
 constexpr int kWholeMaxHalf = 32;  // n <= 64
 
 // Class of a sample by its ellipse centre: kOffDisk, or half the trapezoid

@@ -170,3 +170,16 @@ def test_known_samples(check, tmp_path):
     t = np.array([0.008177178922197671, t1[0]])
     direct, general, _ = run(check, tmp_path, p, t)
     assert np.abs(direct - oracle_flux(p, t)).max() <= 1e-11
+
+
+# rounding of fluxes near 1, and the oracle's own error, which both sides share
+@pytest.mark.parametrize("kind", ["disk"])
+@pytest.mark.parametrize("k_lo,k_hi", [(0.005, 0.05), (0.05, 0.12), (0.12, 0.2), (0.2, 0.35)])
+def test_no_further_off_than_the_general_path(check, tmp_path, kind, k_lo, k_hi):
+    p, t = samples(kind, 8000, k_lo, k_hi, seed=79)
+    direct, general, cls = run(check, tmp_path, p, t)
+    ref = oracle_flux(p, t)
+    for m in (np.isfinite(direct) & (cls >= 0), np.isfinite(direct) & (cls == -1)):
+        assert m.sum() > 200
+        rms = lambda f: np.sqrt(np.mean((f[m] - ref[m]) ** 2))
+        assert rms(direct) <= 1.05 * rms(general) + 1e-15
