@@ -2141,7 +2141,7 @@ struct DirectWhole {
     double a, b, e, f, g0, P0, l1, l2, kap;
     int h;
 };
-constexpr float kNearRate = 34.0f;
+constexpr float kNearRate = 35.5f;
 constexpr int kNearMaxHalf = kHalfSteps;
 
 // Node map of a large shadow's whole ellipse and the distance d of its nearest
@@ -2274,39 +2274,46 @@ GL_HD bool direct_whole(const SH& s, double x0, double y0, DirectWhole& T)
     return true;
 }
 
-// mu integral by the 2h-node rule (nodes psi = +-(2j + 1) pi / (2h))
+// mu integral by the 2h-node rule (nodes psi = +-(2j + 1) pi / (2h)), psi and
+// pi - psi by one rotation of psi/2 below pi/4: the map stretches the nodes close
+// to psi = pi, where 1 + cos(psi) would lose what the rotations have left.
 template <class Reduce>
 GL_HD double whole_rule(const DirectWhole& T, int g, int G, Reduce&& reduce)
 {
     GL_AS_WRITTEN
     const double c1 = kHalfStep.c[T.h], s1 = kHalfStep.s[T.h];
-    const double c2 = fma(-2.0 * s1, s1, 1.0), s2 = 2.0 * s1 * c1;
-    double c = c1, sn = s1, rc = c2, rs = s2;
+    double c = sqrt_nn(fma(0.5, c1, 0.5)), sn = 0.5 * s1 * rcp(c), rc = c1, rs = s1;
     for (int i = 1; i < G; ++i) {
         if (i <= g) {
-            const double cn = fma(c, c2, -(sn * s2));
-            sn = fma(sn, c2, c * s2);
+            const double cn = fma(c, c1, -(sn * s1));
+            sn = fma(sn, c1, c * s1);
             c = cn;
         }
-        const double cn = fma(rc, c2, -(rs * s2));
-        rs = fma(rs, c2, rc * s2);
+        const double cn = fma(rc, c1, -(rs * s1));
+        rs = fma(rs, c1, rc * s1);
         rc = cn;
     }
-    const double k2 = T.kap * T.kap;
     double acc = 0.0;
-    for (int j = g; j < T.h; j += G) {
-        const double up = 1.0 + c, dn = k2 * (1.0 - c), r = rcp_q(up + dn);
-        const double cs = (up - dn) * r, sp = 2.0 * T.kap * sn * r;  // cos p, sin p
-        const double ge = fma(fma(T.e, cs, T.a), cs, T.g0), go = sp * fma(T.f, cs, T.b);
-        const double Le = fma(T.l1, cs, T.P0), Lo = T.l2 * sp;
-        const double o1 = fmax(-ge - go, 0.0), o2 = fmax(go - ge, 0.0);
-        const double D1 = 1.0 + sqrt_q(o1), D2 = 1.0 + sqrt_q(o2);
-        acc = fma(fma((D1 + o1) * (Le + Lo), D2, (D2 + o2) * (Le - Lo) * D1) * rcp_q(D1 * D2), r, acc);
+    for (int j = g; 2 * j < T.h; j += G) {
+        double u = c, v = T.kap * sn;  // tan(p/2) = v / u
+#pragma unroll 1
+        for (int m = 0; m < 2; ++m) {
+            const double up = u * u, dn = v * v, r = rcp_q(up + dn);
+            const double cs = (up - dn) * r, sp = 2.0 * u * v * r;  // cos p, sin p
+            const double ge = fma(fma(T.e, cs, T.a), cs, T.g0), go = sp * fma(T.f, cs, T.b);
+            const double Le = fma(T.l1, cs, T.P0), Lo = T.l2 * sp;
+            const double o1 = fmax(-ge - go, 0.0), o2 = fmax(go - ge, 0.0);
+            const double D1 = 1.0 + sqrt_q(o1), D2 = 1.0 + sqrt_q(o2);
+            acc = fma(fma((D1 + o1) * (Le + Lo), D2, (D2 + o2) * (Le - Lo) * D1) * rcp_q(D1 * D2), r, acc);
+            if (2 * j + 1 == T.h) break;  // psi = pi/2, its own mirror image
+            u = sn;
+            v = T.kap * c;
+        }
         const double cn = fma(c, rc, -(sn * rs));
         sn = fma(sn, rc, c * rs);
         c = cn;
     }
-    return reduce(acc) * (2.0 * T.kap * (kPi / 3.0) * rcp((double)T.h));
+    return reduce(acc) * (T.kap * (kPi / 3.0) * rcp((double)T.h));
 }
 
 // Occulted fraction of a whole ellipse on the disk from its mu integral.

@@ -173,7 +173,7 @@ def test_known_samples(check, tmp_path):
 
 
 # rounding of fluxes near 1, and the oracle's own error, which both sides share
-@pytest.mark.parametrize("kind", ["disk"])
+@pytest.mark.parametrize("kind", ["disk", "limb"])
 @pytest.mark.parametrize("k_lo,k_hi", [(0.005, 0.05), (0.05, 0.12), (0.12, 0.2), (0.2, 0.35)])
 def test_no_further_off_than_the_general_path(check, tmp_path, kind, k_lo, k_hi):
     p, t = samples(kind, 8000, k_lo, k_hi, seed=79)
