@@ -276,7 +276,9 @@ gl_status gl_ctx_set_capacity(gl_ctx *ctx, int64_t sub_samples, int64_t hard_sam
 
 /* A batch of more than 2^26 outputs (or 2^23 workgroups) runs as up to 8 passes
  * over equal ranges of its parameter sets (own grids without a surrogate: 2).  Results do not depend on the
- * number of passes: every sub-sample and output is computed on its own.
+ * number of passes: every sub-sample and output is computed on its own, with the
+ * same bits whatever shares its batch.  (A surrogate batch that runs out of room
+ * for its network's rows is the exception, see gl_lightcurve_batch_surrogate.)
  *
  * gl_ctx_get_overflow waits for the device and writes 0 into *fused_chunks
  * (nothing can overflow: there are no work lists) and into *passes (may be
@@ -292,7 +294,7 @@ gl_status gl_ctx_set_graph(gl_ctx *ctx, int on);
  *  (fills the outputs that cannot overlap the star), 2 classification and
  *  sorting, 3 whole-ellipse trapezoid, 4 crossing ellipses' set-up
  *  (intersection quartic, closed forms), 5 arc rule and near-limb rule,
- *  6 outputs with samples that take the general path, 7 supersample averages,
+ *  6 samples that take the general path, 7 supersample averages,
  *  8 the network and its residuals (surrogate batches).  Stages 1 to 7 are one
  *  launch: its time is shared out by the clocks its wavefronts spent in each
  *  (waits for other wavefronts count for the stage they follow). */
@@ -336,8 +338,9 @@ gl_status gl_census(gl_ctx *ctx, const double *params, int64_t n_sets, const dou
  * intervals. */
 gl_status gl_flop_model(int64_t *per_item);
 
-/* Accuracy report of the arc rule (Section 2: the Green's-theorem line
- * integrals along the ellipse arcs on the star).  Each ellipse arc is
+/* Accuracy report of the general path's arc rule (Section 2: the Green's-theorem line
+ * integrals along the ellipse arcs on the star).  A sample whose direct rule
+ * fails its own check takes that path, where each ellipse arc is
  * integrated by a clustered Gauss-Kronrod 10/21 rule, split into 1, 2, 4, 8
  * and 16 pieces until the Gauss-Kronrod difference is below its tolerance
  * (1e-6; the difference estimates the error of the 10-point Gauss sum, the

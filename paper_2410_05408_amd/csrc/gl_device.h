@@ -1670,7 +1670,9 @@ GL_HD Shape lock_shape(const LK& L, double sa, double ca)
 }
 
 // Whole-ellipse rules: an n-node trapezoid errs like exp(-n d), d the distance
-// of the nearest complex zero of 1 - r^2 from the real axis.
+// of the nearest complex zero of 1 - r^2 from the real axis.  (At an exponent of
+// 23.5 the rms error of planets of k 0.05 to 0.12 is 7.3e-15, at 24 4.6e-15, with
+// 1.6 % more nodes.)
 constexpr float kWholeRate = 24.0f;
 constexpr int kWholeMaxHalf = 32;  // n <= 64
 
@@ -2141,6 +2143,8 @@ struct DirectWhole {
     double a, b, e, f, g0, P0, l1, l2, kap;
     int h;
 };
+// (rms error within 0.3 of the limb, k 0.05 to 0.12: 7.2e-15 at an exponent of 34,
+// 2.5e-15 at 35.5, the general path's 4.4e-15)
 constexpr float kNearRate = 35.5f;
 constexpr int kNearMaxHalf = kHalfSteps;
 

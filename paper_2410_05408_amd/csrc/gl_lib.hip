@@ -498,9 +498,9 @@ __global__ void k_snap_nodes(int n, float2* __restrict__ cs)
 // memory: on the walker batch their traffic, launch gaps and tails were about
 // as long as the arithmetic, and a batch of 64 walkers was all gaps.)
 // Bound by FP64 issue where transits fill the grid (2048 own grids, 20 M
-// outputs: vector units busy about 80 % of the time, 2412 us by the pipeline, 912
+// outputs: vector units busy about 80 % of the time, 2412 us by the pipeline, 890
 // here), by the stores where they do not (512 sets of 65536 outputs, 268 MB:
-// 152 us, here 90), by latency at one set of 1000 (90 us, here 17).
+// 152 us, here 81), by latency at one set of 1000 (90 us, here 16).
 constexpr int kUnit = 1024;      // sub-samples sorted at once
 constexpr int kFluxThreads = 256;
 constexpr int kFluxWaves = kFluxThreads / 64;
@@ -812,9 +812,8 @@ __device__ __forceinline__ void exact_output(const FluxArgs& A, const FluxPlace&
 // the orbit: its samples keep the sine and cosine of their phase in LDS in the
 // place of the centre, and rebuild centre and shadow (lock_shape) where they
 // are classified and where they are evaluated (2048 sets of 1500 outputs, half
-// of them locked: 1031 us by the work lists with a 21-node rule per arc, 255
-// here; 329 at first, at four wavefronts per SIMD and 9 spilled registers, 366 at three, 453
-// at two).
+// of them locked: 1031 us by the work lists with a 21-node rule per arc, 235
+// here; three wavefronts per SIMD instead of four cost 11 %, two 38 %).
 template <bool CENSUS, bool TIMED, int MODE>
 __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
 {

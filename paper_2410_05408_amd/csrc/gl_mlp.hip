@@ -167,7 +167,7 @@ __device__ __forceinline__ bf16x8_t load_op(const bf16* p) { return *reinterpret
 // Bound by the latency of its nine dependent stages and, below that, by the
 // 0.8 MB of weights each block pulls from L2 (64 bytes a clock: 5 us); a
 // stage's weights are loaded while the stage before is finished.  32 rows per
-// block give 256 blocks at 8192 rows, one per CU: 27 us (41 with the weights
+// block give 256 blocks at 8192 rows, one per CU: 26 us (41 with the weights
 // row-major, where an operand touches 16 half lines).
 __global__ void __launch_bounds__(kTrWaves * 64)
 k_train_rows(const float* __restrict__ xf, const bf16* __restrict__ xb, const float* __restrict__ t, int n, TrainBufs B)
@@ -380,7 +380,7 @@ __device__ __forceinline__ void grad_piece(const bf16* __restrict__ in, int64_t 
 }
 
 // Bound by reading the 33 MB of tiles and writing 26 MB of partials (8192
-// rows): 16 us.  A wavefront takes a 64 x 64 piece of a gradient over one row chunk:
+// rows): 15 us.  A wavefront takes a 64 x 64 piece of a gradient over one row chunk:
 // 8 operands for 16 matrix instructions, none through LDS.
 __global__ void __launch_bounds__(256) k_train_sums(SumArgs A)
 {
