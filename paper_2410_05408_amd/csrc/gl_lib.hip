@@ -501,12 +501,16 @@ __global__ void k_snap_nodes(int n, float2* __restrict__ cs)
 // outputs: vector units busy about 80 % of the time, 2412 us by the pipeline, 890
 // here), by the stores where they do not (512 sets of 65536 outputs, 268 MB:
 // 152 us, here 81), by latency at one set of 1000 (90 us, here 16).
-constexpr int kUnit = 1024;      // sub-samples sorted at once
-constexpr int kFluxThreads = 256;
-constexpr int kFluxWaves = kFluxThreads / 64;
-constexpr int kFluxMaxRange = 4096;  // outputs per workgroup at most
-constexpr int kWinRound = 2048;      // outputs whose times are loaded at once
-static_assert(kFluxMaxRange <= 64 * 128 && kFluxMaxRange % kWinRound == 0, "128 outputs per lane");
+// Sizes by the workgroup's wavefronts (see flux_waves): four, or one for many
+// sets of a few outputs.
+template <int WAVES>
+struct FluxSize {
+    static constexpr int unit = 256 * WAVES;  // sub-samples sorted at once
+    static constexpr int range = WAVES == 1 ? 128 : 4096;  // outputs per workgroup at most
+    static constexpr int round = WAVES == 1 ? 128 : 2048;  // outputs whose times are loaded at once
+    static_assert(range <= 64 * 128 && range % round == 0 && round % (128 * WAVES) == 0, "128 outputs per lane");
+};
+constexpr int kFluxWaves = 4;
 // two neighbouring outputs: times and fluxes are 8-byte aligned (a 16-byte
 // access needs 4 here)
 typedef double pair2 __attribute__((ext_vector_type(2), aligned(8)));
@@ -814,20 +818,21 @@ __device__ __forceinline__ void exact_output(const FluxArgs& A, const FluxPlace&
 // are classified and where they are evaluated (2048 sets of 1500 outputs, half
 // of them locked: 1031 us by the work lists with a 21-node rule per arc, 235
 // here; three wavefronts per SIMD instead of four cost 11 %, two 38 %).
-template <bool CENSUS, bool TIMED, int MODE>
-__global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
+template <bool CENSUS, bool TIMED, int MODE, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES, 4) k_flux(FluxArgs A)
 {
     GL_AS_WRITTEN
+    constexpr int kThreads = 64 * WAVES, kUnit = FluxSize<WAVES>::unit, kRange = FluxSize<WAVES>::range, kRound = FluxSize<WAVES>::round;
     __shared__ double fx[kUnit], fy[kUnit];        // ellipse centres; fx then holds the fluxes
     __shared__ unsigned short ord[kUnit + 128];    // sorted entries: index | order << 10
     // in-window outputs of the range, per 128 of them the even ones, then the odd
-    __shared__ unsigned long long masks[kFluxMaxRange / 64];
-    __shared__ unsigned short win[kFluxMaxRange];             // their offsets in it
+    __shared__ unsigned long long masks[kRange / 64];
+    __shared__ unsigned short win[kRange];             // their offsets in it
     __shared__ int cnt[64];
     __shared__ unsigned short dec[kUnit];          // entries that the direct rules declined
     __shared__ int n_wide, n_hard, n_whole, next_tile, n_dec, any_nonet;
     // surrogate: outputs without room for their rows; rows per 64 entries; the unit's first row
-    __shared__ unsigned int nonet[MODE == M_SURROGATE ? kFluxMaxRange / 32 : 1];
+    __shared__ unsigned int nonet[MODE == M_SURROGATE ? kRange / 32 : 1];
     __shared__ int net_n[kUnit / 64 + 1];
     __shared__ long long net_at;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -848,7 +853,7 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
             t_last = t;
         }
     };
-    if (MODE == M_SURROGATE && tid < kFluxMaxRange / 32) nonet[tid] = 0u;
+    if (MODE == M_SURROGATE && tid < kRange / 32) nonet[tid] = 0u;
     unsigned int n_sub = 0u, n_on = 0u, n_acc = 0u;  // surrogate: in window, on the disk, accepted
     if (tid == 0) any_nonet = 0;
     {
@@ -862,10 +867,10 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
             const double dt = v - t0;
             return fabs(fma(-P, rint(dt * inv_P), dt));
         };
-        for (int k0 = 0; k0 < n_range; k0 += kWinRound) {
-            constexpr int nk = kWinRound / 128 / kFluxWaves;
+        for (int k0 = 0; k0 < n_range; k0 += kRound) {
+            constexpr int nk = kRound / 128 / WAVES;
             pair2 t[nk];
-            if (valid && k0 + kWinRound <= n_range) {
+            if (valid && k0 + kRound <= n_range) {
                 // a whole round out of transit, the usual one where transits
                 // are rare: one test, then stores alone, streamed past the
                 // caches (the 1s are never read back)
@@ -873,7 +878,7 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
                 bool in = false;
                 const int pos = k0 + 128 * wv + 2 * lane;
 #pragma unroll
-                for (int k = 0; k < nk; ++k) t[k] = *(const pair2*)(times + pos + 128 * kFluxWaves * k);
+                for (int k = 0; k < nk; ++k) t[k] = *(const pair2*)(times + pos + 128 * WAVES * k);
 #pragma unroll
                 for (int k = 0; k < nk; ++k) {
                     a[2 * k] = phase(t[k].x);
@@ -884,21 +889,21 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
                 if (!__ballot(in)) {
 #pragma unroll
                     for (int k = 0; k < nk; ++k)
-                        __builtin_nontemporal_store(pair2{1.0, 1.0}, (pair2*)(out + pos + 128 * kFluxWaves * k));
-                    if (lane < 2 * nk) masks[(k0 >> 6) + (lane >> 1) * (2 * kFluxWaves) + 2 * wv + (lane & 1)] = 0ull;
+                        __builtin_nontemporal_store(pair2{1.0, 1.0}, (pair2*)(out + pos + 128 * WAVES * k));
+                    if (lane < 2 * nk) masks[(k0 >> 6) + (lane >> 1) * (2 * WAVES) + 2 * wv + (lane & 1)] = 0ull;
                     continue;
                 }
             } else {
 #pragma unroll
                 for (int k = 0; k < nk; ++k) {
-                    const int pos = k0 + 128 * (k * kFluxWaves + wv) + 2 * lane;
+                    const int pos = k0 + 128 * (k * WAVES + wv) + 2 * lane;
                     t[k] = pair2{pos < n_range ? times[pos] : 0.0, pos + 1 < n_range ? times[pos + 1] : 0.0};
                 }
             }
             unsigned int odd = 0u;  // groups of 128 with a value that is not finite, or of an invalid set
 #pragma unroll
             for (int k = 0; k < nk; ++k) {
-                const int g = k0 + 128 * (k * kFluxWaves + wv), pos = g + 2 * lane;
+                const int g = k0 + 128 * (k * WAVES + wv), pos = g + 2 * lane;
                 unsigned long long m0 = 0ull, m1 = 0ull;
                 if (g < n_range) {
                     const double a0 = phase(t[k].x), a1 = phase(t[k].y);
@@ -923,7 +928,7 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
 #pragma unroll 1
                 for (int k = 0; k < nk; ++k) {
                     if (!((odd >> k) & 1u)) continue;
-                    const int g = k0 + 128 * (k * kFluxWaves + wv);
+                    const int g = k0 + 128 * (k * WAVES + wv);
 #pragma unroll 1
                     for (int i = 0; i < 2; ++i) {
                         const int pos = g + 2 * lane + i;
@@ -945,18 +950,18 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
         }
         // positions of the in-window outputs, in order, 128 outputs per lane
         // (masks beyond the range's last round were not written)
-        const bool mine = lane < (n_range + kWinRound - 1) / kWinRound * (kWinRound / 128);
+        const bool mine = lane < (n_range + kRound - 1) / kRound * (kRound / 128);
         int incl = mine ? __popcll(masks[2 * lane]) + __popcll(masks[2 * lane + 1]) : 0;
         const bool some = incl != 0;
-        for (int d = 1; d < kFluxMaxRange / 128; d <<= 1) {
+        for (int d = 1; d < kRange / 128; d <<= 1) {
             const int v = __shfl_up(incl, d);
             if (lane >= d) incl += v;
         }
-        const int n_in = __shfl(incl, kFluxMaxRange / 128 - 1);
+        const int n_in = __shfl(incl, kRange / 128 - 1);
         // (those with any are few and neighbours where transits are rare)
         int turn = 0;
         for (unsigned long long nz = __ballot(some); nz; nz &= nz - 1ull)
-            if ((turn++ & (kFluxWaves - 1)) == wv) {
+            if ((turn++ & (WAVES - 1)) == wv) {
                 const int g = __builtin_ctzll(nz);
                 const unsigned long long m0 = masks[2 * g], m1 = masks[2 * g + 1];
                 const int first = __builtin_amdgcn_readlane(incl, g) - __popcll(m0) - __popcll(m1);
@@ -983,7 +988,7 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
             int jj[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const int e = k * kFluxThreads + tid;
+                const int e = k * kThreads + tid;
                 ts[k] = 0.0;
                 jj[k] = 0;
                 if (e < N) {
@@ -1009,7 +1014,7 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
             bool net[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const int e = k * kFluxThreads + tid;
+                const int e = k * kThreads + tid;
                 val[k] = 0;
                 net[k] = false;
                 bool sphere = false;
@@ -1056,7 +1061,7 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
                 place[k] = b;
                 if (MODE == M_SURROGATE) {
                     const unsigned long long mn = __ballot(net[k]);
-                    if (lane == 0) net_n[k * kFluxWaves + wv] = __popcll(mn);
+                    if (lane == 0) net_n[k * WAVES + wv] = __popcll(mn);
                 }
             }
             // ranks in the buckets: the lanes that share a lane's bucket from
@@ -1135,8 +1140,8 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
                     const bool mine = k == 0 ? net[0] : k == 1 ? net[1] : k == 2 ? net[2] : net[3];
                     const unsigned long long mn = __ballot(mine);
                     if (!mine) continue;
-                    const int e = k * kFluxThreads + tid, o = win[o0 + (int)(((float)e + 0.5f) * inv_nss_f)];
-                    const int64_t row = at + net_n[k * kFluxWaves + wv] + lanes_below(mn);
+                    const int e = k * kThreads + tid, o = win[o0 + (int)(((float)e + 0.5f) * inv_nss_f)];
+                    const int64_t row = at + net_n[k * WAVES + wv] + lanes_below(mn);
                     if (!fits) {
                         // no room: the output is exact, a slot below the end is empty
                         atomicOr(&nonet[o >> 5], 1u << (o & 31));
@@ -1261,7 +1266,7 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
             __syncthreads();
             if (const int nd = __builtin_amdgcn_readfirstlane(n_dec); __builtin_expect(nd, 0)) {
                 // declined
-                for (int i = fresh_v(threadIdx.x); i < nd; i += kFluxThreads) {
+                for (int i = fresh_v(threadIdx.x); i < nd; i += kThreads) {
                     const int v = dec[i], e = v & 1023;
                     const gl::SetConst* s = (MODE == M_SURROGATE && (v & 0x8000) ? A.net.sph : A.sc) + si;
                     const FluxU r = flux_declined<CENSUS, MODE>(*s, fx[e], fy[e], tally);
@@ -1273,7 +1278,7 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
             }
             __builtin_amdgcn_s_setprio(kPrioLatency);
             // average
-            for (int o = fresh_v(threadIdx.x); o < no; o += kFluxThreads) {
+            for (int o = fresh_v(threadIdx.x); o < no; o += kThreads) {
                 double sum = 0.0;
                 for (int j = 0; j < nss; ++j) sum += fx[o * nss + j];
                 const int w = win[o0 + o];
@@ -1285,9 +1290,9 @@ __global__ void __launch_bounds__(kFluxThreads, 4) k_flux(FluxArgs A)
     }
     if (MODE == M_SURROGATE && __builtin_amdgcn_readfirstlane(any_nonet)) {
         int turn = 0;
-        for (int w = 0; w < kFluxMaxRange / 32; ++w)
+        for (int w = 0; w < kRange / 32; ++w)
             for (unsigned int bits = __builtin_amdgcn_readfirstlane(nonet[w]); bits; bits &= bits - 1u)
-                if ((turn++ & (kFluxWaves - 1)) == wv) exact_output(A, pl, 32 * w + __builtin_ctz(bits), unconv);
+                if ((turn++ & (WAVES - 1)) == wv) exact_output(A, pl, 32 * w + __builtin_ctz(bits), unconv);
         lap(C_DECLINED);
     }
     if (CENSUS)
@@ -1499,6 +1504,7 @@ struct Batch {
     int64_t ld = 0;          // row stride of params (the whole batch's n_sets)
     int first = 1, last = 1;  // first / last pass of the batch
     int range = 128;         // outputs per workgroup of the fused pass
+    int waves = kFluxWaves;  // and its wavefronts
     // surrogate batches (net != NULL): the gate and the network
     gl_mlp* net = nullptr;
     const float* gate_table = nullptr;
@@ -1570,6 +1576,23 @@ gl_status record_event(gl_ctx* ctx, hipEvent_t ev, hipStream_t s, int e)
     return fail(ctx, GL_ERR_DEVICE, what, r);
 }
 
+// Wavefronts per workgroup of the fused pass.  A workgroup's outputs are one set's,
+// so many sets of a few outputs leave four wavefronts mostly idle: with one,
+// four times as many sets are on the chip at once.  Its chain is longer, so the
+// sub-samples of a set must be few or the sets several times what the chip holds
+// (4096); without n_ss the outputs are the sub-samples, with it (its values are
+// on the device) fewer outputs qualify.  One wavefront against four, us:
+//   65536 sets of 1 output: 138, 454; of 10: 245, 593 (x 64: 1061, 1140); of 32:
+//   295, 629 (x 15: 1060, 1023); of 128: 413, 714; 16384 of 10: 83, 162 (x 64:
+//   339, 309); of 32 x 15: 326, 278; 4096 of 1: 25, 43 (x 64: 53, 56); of 10 x 64:
+//   155, 118; of 128: 58, 63; 1024 of 10: 29, 26.
+int flux_waves(const Batch& b)
+{
+    const int64_t n = b.offsets ? b.n_times : b.n_sets * b.n_times;
+    const int64_t most = b.n_ss ? std::min<int64_t>(32, b.n_sets / 1024) : FluxSize<1>::range;
+    return b.n_sets >= 4096 && n <= most * b.n_sets ? 1 : kFluxWaves;
+}
+
 // Outputs per workgroup of the fused pass (CSR: at most): enough workgroups to
 // fill the chip (1024 are resident) four times over, at most 4096 outputs each
 // (512 sets of 65536: 91 us at 2048, 89 at 4096; 2048 own grids: 971 and 947;
@@ -1579,15 +1602,16 @@ gl_status record_event(gl_ctx* ctx, hipEvent_t ev, hipStream_t s, int e)
 // An own grid's workgroups shrink with its supersampling (flux_range_of), so
 // half as many outputs' worth of them are asked for (3 M outputs: 351 us at
 // 4096, 315 at 2048; 333 sets of 1777 shared times: 62 us at 4096, 74 at 2048).
-constexpr int kFluxTop = 4096, kFluxWant = 4096, kFluxWantOwn = 2048;
+constexpr int kFluxTop = FluxSize<kFluxWaves>::range, kFluxWant = 4096, kFluxWantOwn = 2048;
 int flux_range(const Batch& b)
 {
+    if (b.waves == 1) return b.offsets ? FluxSize<1>::range : (int)((b.n_times + 63) / 64 * 64);
     const int64_t n = b.offsets ? b.n_times / kFluxWantOwn : b.n_sets * b.n_times / kFluxWant;
     int r = kFluxMinRange;
     while (2 * r <= n && r < kFluxTop) r *= 2;
     if (b.offsets) return r;
     // a set's workgroups of equal length, and none for a short remainder
-    const int64_t per_set = std::max<int64_t>((b.n_times + kFluxMaxRange - 1) / kFluxMaxRange, (b.n_times + r / 4) / r);
+    const int64_t per_set = std::max<int64_t>((b.n_times + kFluxTop - 1) / kFluxTop, (b.n_times + r / 4) / r);
     return (int)(((b.n_times + per_set - 1) / per_set + 63) / 64 * 64);
 }
 
@@ -1597,6 +1621,15 @@ int64_t flux_blocks(const Batch& b)
 {
     return b.offsets ? b.n_times / kFluxMinRange + b.n_sets : (b.n_times + b.range - 1) / b.range * b.n_sets;
 }
+
+template <bool CENSUS, int WAVES>
+auto flux_kernel(const Batch& b, bool timed)
+{
+    return b.net          ? (timed ? k_flux<false, true, M_SURROGATE, WAVES> : k_flux<false, false, M_SURROGATE, WAVES>)
+           : b.shape == 1 ? (timed ? k_flux<false, true, M_ELLIPSOID, WAVES> : k_flux<CENSUS, false, M_ELLIPSOID, WAVES>)
+                          : (timed ? k_flux<false, true, M_OBLATE, WAVES> : k_flux<CENSUS, false, M_OBLATE, WAVES>);
+}
+
 // One pass of the exact path: set-up, then the fused pass.
 template <bool CENSUS>
 gl_status enqueue_flux(gl_ctx* ctx, const Batch& b)
@@ -1649,10 +1682,9 @@ gl_status enqueue_flux(gl_ctx* ctx, const Batch& b)
         A.net.k = b.gate_k;
         A.net.sph = ctx->sc_sph;
     }
-    auto flux = b.net          ? (ev ? k_flux<false, true, M_SURROGATE> : k_flux<false, false, M_SURROGATE>)
-                : b.shape == 1 ? (ev ? k_flux<false, true, M_ELLIPSOID> : k_flux<CENSUS, false, M_ELLIPSOID>)
-                               : (ev ? k_flux<false, true, M_OBLATE> : k_flux<CENSUS, false, M_OBLATE>);
-    hipLaunchKernelGGL(flux, dim3(A.row, (unsigned)((grid + A.row - 1) / A.row)), dim3(kFluxThreads), 0, st, A);
+    const bool timed = ev != nullptr;
+    auto flux = b.waves == 1 ? flux_kernel<CENSUS, 1>(b, timed) : flux_kernel<CENSUS, kFluxWaves>(b, timed);
+    hipLaunchKernelGGL(flux, dim3(A.row, (unsigned)((grid + A.row - 1) / A.row)), dim3(64 * b.waves), 0, st, A);
     if (ev && record_event(ctx, ev[E_FUSED], st, E_FUSED) != GL_OK) return GL_ERR_DEVICE;
     if (b.net) {
         gl_net::infer(b.net, A.net.x, A.net.cap, &ctx->ctr->net_total, A.net.y, st);
@@ -1713,6 +1745,7 @@ gl_status prepare_batch(gl_ctx* ctx, Batch& b)
 {
     // passes over equal ranges of sets, so that no launch covers more than
     // about kPassOut outputs or kPassBlocks workgroups
+    b.waves = flux_waves(b);
     b.range = flux_range(b);
     const int64_t n = b.offsets ? b.n_times : b.n_sets * b.n_times;
     const int64_t blocks = flux_blocks(b);
@@ -2327,6 +2360,7 @@ extern "C" gl_status gl_lightcurve_batch_noalloc(const double* params, int64_t n
     c.passes = 1;
     // (nothing to clear: k_prep writes the counters this call reads, and the
     // status is not reported)
+    b.waves = flux_waves(b);
     b.range = flux_range(b);
     return enqueue_flux<false>(&c, b);
 }

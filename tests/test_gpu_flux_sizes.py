@@ -189,3 +189,94 @@ def test_bits_of_a_sample_alone(gpu_lib, ctx):
     alone = W.Workload("alone", np.ascontiguousarray(np.repeat(p, t.size, axis=1)), np.tile(t, 4),
                        np.arange(n + 1, dtype=np.int64), np.ones(n, np.int32), np.zeros(n), {})
     assert np.array_equal(got, flux(gpu_lib, ctx, alone).reshape(4, -1))
+
+
+def _many(n, seed):
+    # planets up to k = 0.9, some of whose samples the direct rules decline
+    from paper_2410_05408_amd import workloads as W
+    rng = np.random.default_rng(seed)
+    p = W.walker_batch(n_sets=n).params
+    p[W.B], p[W.T0] = rng.uniform(0.0, 1.0, n), 0.0
+    p[W.K, ::7] = rng.uniform(0.2, 0.9, p[W.K, ::7].size)
+    p[W.P, 11] = -1.0  # an invalid set
+    return np.ascontiguousarray(p)
+
+
+def _in_parts(run, n, *cols):
+    # the same sets in batches too small for workgroups of one wavefront
+    return np.concatenate([run(*(None if c is None else np.ascontiguousarray(c[..., a:a + 1500]) for c in cols))
+                           for a in range(0, n, 1500)])
+
+
+@pytest.mark.parametrize("n_sets,n_times,n_ss", [(4096, 1, 64), (4100, 4, 0), (4097, 128, None), (4099, 65, None),
+                                                 (16384, 16, 15), (16385, 13, 0), (33000, 32, 5)])
+def test_many_small_sets_shared(gpu_lib, ctx, n_sets, n_times, n_ss):
+    import torch
+    print(f"case: {n_sets} sets of {n_times} shared outputs of {n_ss} sub-samples", flush=True)
+    p, t = _many(n_sets, 3), np.linspace(-0.3, 0.35, n_times) if n_times > 1 else np.array([0.05])
+    if n_times > 2:
+        t[1] = np.nan
+    ss = None if n_ss is None else np.random.default_rng(5).integers(1, 65, n_sets).astype(np.int32) if n_ss == 0 else \
+        np.full(n_sets, n_ss, np.int32)
+    te = np.full(n_sets, 0.02)
+    dev = lambda a: None if a is None else torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+    def run(p, ss, te):
+        out = ctx.batch(dev(p), dev(t), n_ss=dev(ss), t_exp=dev(te)).cpu().numpy().reshape(p.shape[1], -1)
+        gpu_lib.gl_ctx_sync_status(ctx.handle)
+        return out
+
+    got = run(p, ss, te)
+    assert np.array_equal(got, _in_parts(run, n_sets, p, ss, te), equal_nan=True)
+    ok = np.delete(got, 11, axis=0)
+    assert np.isnan(got[11]).all() and np.isfinite(np.delete(ok, 1, axis=1) if n_times > 2 else ok).all()
+
+
+@pytest.mark.parametrize("kind", ["oblate", "ellipsoid"])
+def test_many_small_sets_own(gpu_lib, ctx, kind):
+    import torch
+    from paper_2410_05408_amd import workloads as W
+    print(f"case: 5000 own grids of 0 to 7 outputs and two of 300 and 129, {kind}", flush=True)
+    n, rng = 5000, np.random.default_rng(8)
+    p = _many(n, 4) if kind == "oblate" else np.concatenate([W.draw_ellipsoids(rng, n // 2, True), W.draw_ellipsoids(rng, n // 2, False)], axis=1)
+    lens = rng.integers(0, 8, n)
+    lens[[17, 4000]] = 300, 129
+    ss, te = rng.integers(1, 20, n).astype(np.int32), np.full(n, 0.01)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    t = rng.uniform(-0.3, 0.3, off[-1])
+    t[off[17] + 150] = np.inf
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    call = ctx.batch if kind == "oblate" else ctx.batch_ellipsoid
+
+    def run(a, e):
+        out = call(dev(p[:, a:e]), dev(t[off[a]:off[e]]), offsets=dev(off[a:e + 1] - off[a]), n_ss=dev(ss[a:e]), t_exp=dev(te[a:e]))
+        out = out.cpu().numpy()
+        gpu_lib.gl_ctx_sync_status(ctx.handle)
+        return out
+
+    got = run(0, n)
+    assert np.array_equal(got, np.concatenate([run(a, min(n, a + 1500)) for a in range(0, n, 1500)]), equal_nan=True)
+    assert np.isnan(got[off[17] + 150]) and np.isfinite(np.delete(got[off[12]:], off[17] + 150 - off[12])).all()
+
+
+def test_many_small_sets_other_calls(gpu_lib, ctx):
+    # the allocation-free call, a timed batch and a census give the same bits
+    import torch
+    gl = gpu_lib
+    print("case: 4500 sets of 4 shared outputs of 3 sub-samples by every call", flush=True)
+    n, t = 4500, np.linspace(-0.2, 0.2, 4)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    d, td, ss, te = dev(_many(n, 6)), dev(t), dev(np.full(n, 3, np.int32)), dev(np.full(n, 0.01))
+    new = lambda: torch.full((n * 4,), -1.0, dtype=torch.float64, device="cuda")
+    outs = [new() for _ in range(4)]
+    gl.gl_lightcurve_batch(ctx.handle, d, td, outs[0], n_ss=ss, t_exp=te)
+    gl.gl_lightcurve_batch_noalloc(d, td, outs[1], n_ss=ss, t_exp=te)
+    gl.gl_ctx_set_timing(ctx.handle, 1)
+    gl.gl_lightcurve_batch(ctx.handle, d, td, outs[2], n_ss=ss, t_exp=te)
+    gl.gl_ctx_set_timing(ctx.handle, 0)
+    census = gl.gl_census(ctx.handle, d, td, outs[3], n_ss=ss, t_exp=te)
+    torch.cuda.synchronize()
+    gl.gl_ctx_sync_status(ctx.handle)
+    assert census["sub_in_window"] > 4 * n
+    for o in outs[1:]:
+        assert np.array_equal(outs[0].cpu().numpy(), o.cpu().numpy(), equal_nan=True)

@@ -80,3 +80,27 @@ def test_first_batch_of_two_million_rows(gpu_lib, tmp_path):
         assert sur.lightcurve(d, out, tol=1e-6) == (n_sets * n_times * n_ss, 0)
         outs.append(out)
     assert torch.equal(outs[0], outs[1])
+
+
+def test_many_small_sets(gpu_lib, tmp_path):
+    # workgroups of one wavefront: the same bits as in batches of fewer sets
+    import torch
+    from paper_2410_05408_amd import workloads as W
+    gl = gpu_lib
+    print("case: 4200 sets of 4 outputs of 5 sub-samples", flush=True)
+    n = 4200
+    p = W.walker_batch(n_sets=n).params
+    p[W.B], p[W.T0] = 0.3, 0.0
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    t = np.linspace(-0.3, 0.3, 4)
+    ctx = gl.Context(0)
+    sur = _surrogate(gl, ctx, str(tmp_path / "s.bin"))
+
+    def run(q):
+        m = q.shape[1]
+        out = torch.empty(m * t.size, dtype=torch.float64, device="cuda")
+        sur.lightcurve({"params": dev(q), "times": dev(t), "offsets": None, "n_ss": dev(np.full(m, 5, np.int32)),
+                        "t_exp": dev(np.full(m, 0.02))}, out, tol=1e-6)
+        return out.cpu().numpy()
+
+    assert np.array_equal(run(p), np.concatenate([run(p[:, a:a + 1400]) for a in range(0, n, 1400)]))
