@@ -75,11 +75,21 @@ struct Counters {
 // 1070 at 8192 and 1208 at 16384, where the last ones hold the launch up; with
 // the smaller ones at the end, see most_of, 971 at 4096 and 947 at 8192).
 constexpr int kFluxMinRange = 128;
-__device__ __forceinline__ int flux_range_of(int most, int nss)
+// Fewer outputs where the workgroups would not fill the chip: a range is halved as
+// often as the launch has room for (flux_halvings), down to kFluxFew sub-samples
+// (768: 16 sets of 3000 x 3 60 us, 44 at 512; 256: 256 sets of 1000 x 3 57, 50 at 512).
+constexpr int kFluxFew = 512;
+__host__ __device__ __forceinline__ int flux_halved(int range, int nss, int halvings)
+{
+    for (int h = 0; h < halvings && range * nss > kFluxFew; ++h) range = ((range >> 1) + 1) & ~1;
+    return range;
+}
+
+__device__ __forceinline__ int flux_range_of(int most, int nss, int halvings)
 {
     int r = kFluxMinRange;
     while (r * nss <= most && 2 * r <= most) r *= 2;
-    return r;
+    return flux_halved(r, nss, halvings);
 }
 
 // The last eighth of a batch's own grids takes workgroups a quarter as large,
@@ -106,7 +116,8 @@ __global__ void k_prep(const double* __restrict__ params, int64_t ld, int64_t n_
                        int64_t* __restrict__ seg_len, int64_t* __restrict__ chunk_off,
                        Counters* __restrict__ ctr, int64_t cps_shared, int first, int last,
                        gl::SetConst* __restrict__ sph, const double* __restrict__ sigma,
-                       int64_t n_sigma, double* __restrict__ norm, int fused_range, int64_t scan_most, int clear)
+                       int64_t n_sigma, double* __restrict__ norm, int fused_range, int halvings, int64_t scan_most,
+                       int clear)
 {
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (s == 0) ctr->net_total = 0ull;
@@ -183,7 +194,7 @@ __global__ void k_prep(const double* __restrict__ params, int64_t ld, int64_t n_
                 ctr->total_chunks = (unsigned long long)(n_sets * cps_shared);
             }
         } else if (offsets) {
-            const int64_t per = fused_range ? flux_range_of(most_of(fused_range, s, n_sets), ok ? nss : 1) : kChunk;
+            const int64_t per = fused_range ? flux_range_of(most_of(fused_range, s, n_sets), ok ? nss : 1, halvings) : kChunk;
             count = (e - b + per - 1) / per;
             if (!scan_most) chunk_off[s] = count;
         }
@@ -740,7 +751,8 @@ struct FluxArgs {
     Counters* ctr;
     double* out;
     int range;                 // outputs per workgroup (CSR: at most, see flux_range_of)
-    unsigned int per_set;      // shared grid: workgroups per set
+    int halvings;              // and how often it may be halved (flux_halved)
+    unsigned int per_set;      // shared grid: workgroups per set, at most
     unsigned int row;          // workgroups per row of the launch's grid (gl::flux_row)
     NetArgs net;               // surrogate passes
 };
@@ -770,7 +782,7 @@ __device__ __forceinline__ FluxPlace flux_place(const FluxArgs& A, unsigned int 
         if ((int64_t)blk >= A.blk_off[A.n_sets]) return p;
         const int64_t s = set_of_block(A.blk_off, A.n_sets, blk);
         p.set = __builtin_amdgcn_readfirstlane((int)s);
-        const int range = flux_range_of(most_of(A.range, s, A.n_sets), A.sc[s].valid ? A.sc[s].n_ss : 1);
+        const int range = flux_range_of(most_of(A.range, s, A.n_sets), A.sc[s].valid ? A.sc[s].n_ss : 1, A.halvings);
         const int64_t b0 = uniform64(A.blk_off[s]), count = uniform64(A.blk_off[s + 1]) - b0;
         const int64_t r0 = turned((int64_t)blk - b0, s, count) * __builtin_amdgcn_readfirstlane(range);
         const int64_t first = uniform64(A.seg_begin[s]) + r0;
@@ -778,11 +790,31 @@ __device__ __forceinline__ FluxPlace flux_place(const FluxArgs& A, unsigned int 
         p.times = A.times + first;
         p.out = A.out + first;
     } else {
-        const unsigned int q = blk / A.per_set;
+        unsigned int q = blk / A.per_set;
         if ((int64_t)q >= A.n_sets) return p;
-        const int64_t r0 = turned(blk - q * A.per_set, q, A.per_set) * A.range;
+        int range = A.range;
+        int64_t r = blk - q * A.per_set;
+        if (A.halvings) {
+            // the sets' first workgroups first: those that their n_ss leaves
+            // without outputs come last, beside the others' work (64 walkers of
+            // 1009 x 3: 36.6 us set by set); turned by one set in each round, or
+            // all of a heavy set's would meet on one XCD (16 sets of 3000 x 64:
+            // 249 us)
+            const unsigned int n = (unsigned int)A.n_sets, i = blk / n, k = blk - i * n + i % n;
+            r = i;
+            q = k >= n ? k - n : k;
+            // (n_ss together with the constants that the window test reads next)
+            const gl::SetConst* sp = A.sc + q;
+            const int nss = sload(&sp->n_ss);
+            const double t0 = sload(&sp->t0), win = sload(&sp->half_win);
+            asm volatile("" ::"s"(nss), "s"(t0), "s"(win));
+            range = flux_halved(range, std::min(std::max(nss, 1), 64), A.halvings);
+        } else {
+            r = turned(r, q, A.per_set);
+        }
+        const int64_t r0 = r * range;
         p.set = (int)q;
-        p.n = (int)std::min<int64_t>(A.range, A.n_times - r0);
+        p.n = (int)std::max<int64_t>(std::min<int64_t>(range, A.n_times - r0), 0);
         p.times = A.times + r0;
         p.out = A.out + ((int64_t)q * A.n_times + r0);
     }
@@ -1504,7 +1536,8 @@ struct Batch {
     int64_t ld = 0;          // row stride of params (the whole batch's n_sets)
     int first = 1, last = 1;  // first / last pass of the batch
     int range = 128;         // outputs per workgroup of the fused pass
-    int waves = kFluxWaves;  // and its wavefronts
+    int halvings = 0;        // how often they may be halved
+    int waves = kFluxWaves;  // its wavefronts
     // surrogate batches (net != NULL): the gate and the network
     gl_mlp* net = nullptr;
     const float* gate_table = nullptr;
@@ -1583,13 +1616,13 @@ gl_status record_event(gl_ctx* ctx, hipEvent_t ev, hipStream_t s, int e)
 // (4096); without n_ss the outputs are the sub-samples, with it (its values are
 // on the device) fewer outputs qualify.  One wavefront against four, us:
 //   65536 sets of 1 output: 138, 454; of 10: 245, 593 (x 64: 1061, 1140); of 32:
-//   295, 629 (x 15: 1060, 1023); of 128: 413, 714; 16384 of 10: 83, 162 (x 64:
+//   295, 629 (x 15: 1060, 1023); of 64 x 5: 874, 876; of 128: 413, 714; 16384 of 10: 83, 162 (x 64:
 //   339, 309); of 32 x 15: 326, 278; 4096 of 1: 25, 43 (x 64: 53, 56); of 10 x 64:
 //   155, 118; of 128: 58, 63; 1024 of 10: 29, 26.
 int flux_waves(const Batch& b)
 {
     const int64_t n = b.offsets ? b.n_times : b.n_sets * b.n_times;
-    const int64_t most = b.n_ss ? std::min<int64_t>(32, b.n_sets / 1024) : FluxSize<1>::range;
+    const int64_t most = b.n_ss ? std::min<int64_t>(FluxSize<1>::range, b.n_sets / 1024) : FluxSize<1>::range;
     return b.n_sets >= 4096 && n <= most * b.n_sets ? 1 : kFluxWaves;
 }
 
@@ -1619,7 +1652,24 @@ int flux_range(const Batch& b)
 // the device only).
 int64_t flux_blocks(const Batch& b)
 {
-    return b.offsets ? b.n_times / kFluxMinRange + b.n_sets : (b.n_times + b.range - 1) / b.range * b.n_sets;
+    const int least = flux_halved(b.offsets ? kFluxMinRange : b.range, 64, b.halvings);
+    return b.offsets ? b.n_times / least + b.n_sets : (b.n_times + least - 1) / least * b.n_sets;
+}
+
+// How often the workgroups' ranges may be halved (the device knows n_ss, and how
+// often it pays; the workgroups left over end at once): to at most 4096 workgroups,
+// four times what the chip holds.  A workgroup's units follow one another, so
+// few sets of many sub-samples were a long chain on a part of the chip: 16 sets of
+// 1000 x 15 100 us without, 58 with, of 1000 x 64 292 and 94, one of 3000 x 64 144
+// and 25; to at most 2048, 64 sets of 3000 x 15 133, not 108.
+constexpr int64_t kFluxFill = 4096;
+int flux_halvings(Batch b)
+{
+    if (!b.n_ss || b.waves == 1) return 0;
+    b.halvings = 0;
+    int h = 0;
+    for (int64_t n = 2 * flux_blocks(b); n <= kFluxFill && h < 4; n *= 2) ++h;
+    return h;
 }
 
 template <bool CENSUS, int WAVES>
@@ -1660,13 +1710,14 @@ gl_status enqueue_flux(gl_ctx* ctx, const Batch& b)
     A.ctr = ctx->ctr;
     A.out = b.out;
     A.range = b.range;
-    A.per_set = (unsigned int)((b.n_times + b.range - 1) / b.range);
+    A.halvings = b.halvings;
     const int64_t grid = flux_blocks(b);
+    A.per_set = (unsigned int)(shared ? grid / b.n_sets : 0);
     A.row = gl::flux_row(grid);
     hipLaunchKernelGGL(prep, dim3(prep_blocks), dim3(prep_threads), 0, st, b.params, b.ld, b.n_sets, b.offsets, b.n_times,
                        b.n_ss, b.t_exp, ctx->sc, ctx->seg_begin, ctx->seg_len, ctx->chunk_off, ctx->ctr,
                        (int64_t)0, b.first, b.last, b.net ? ctx->sc_sph : nullptr, b.sigma, b.n_times,
-                       norm ? &ctx->ctr->ll_norm : nullptr, (int)b.range, scan_here ? grid : (int64_t)0,
+                       norm ? &ctx->ctr->ll_norm : nullptr, (int)b.range, b.halvings, scan_here ? grid : (int64_t)0,
                        b.first && (CENSUS || ev || b.net));
     if (!shared) {
         if (!scan_here) hipLaunchKernelGGL(k_scan, dim3(1), dim3(kScanThreads), 0, st, ctx->chunk_off, b.n_sets, grid, ctx->ctr);
@@ -1747,6 +1798,7 @@ gl_status prepare_batch(gl_ctx* ctx, Batch& b)
     // about kPassOut outputs or kPassBlocks workgroups
     b.waves = flux_waves(b);
     b.range = flux_range(b);
+    b.halvings = flux_halvings(b);
     const int64_t n = b.offsets ? b.n_times : b.n_sets * b.n_times;
     const int64_t blocks = flux_blocks(b);
     const int64_t want = std::max((n + kPassOut - 1) / kPassOut, (blocks + kPassBlocks - 1) / kPassBlocks);
@@ -2241,7 +2293,7 @@ gl_status gl_lightcurve_batch_snap(gl_ctx* ctx, int n_nodes, const double* param
     const int64_t cps_shared = shared ? (b.n_times + kChunk - 1) / kChunk : 0;
     hipLaunchKernelGGL(k_prep<0>, dim3((unsigned)((n_sets + 255) / 256)), dim3(256), 0, s, params, n_sets, n_sets,
                        offsets, n_times, n_ss, t_exp, ctx->sc, ctx->seg_begin, ctx->seg_len, ctx->chunk_off, ctx->ctr,
-                       cps_shared, 1, 1, (gl::SetConst*)nullptr, (const double*)nullptr, (int64_t)0, (double*)nullptr, 0, (int64_t)0, 0);
+                       cps_shared, 1, 1, (gl::SetConst*)nullptr, (const double*)nullptr, (int64_t)0, (double*)nullptr, 0, 0, (int64_t)0, 0);
     if (!shared)
         hipLaunchKernelGGL(k_scan, dim3(1), dim3(kScanThreads), 0, s, ctx->chunk_off, n_sets, b.max_chunks, ctx->ctr);
     launch_window(ctx, b, s);
@@ -2362,6 +2414,7 @@ extern "C" gl_status gl_lightcurve_batch_noalloc(const double* params, int64_t n
     // status is not reported)
     b.waves = flux_waves(b);
     b.range = flux_range(b);
+    b.halvings = flux_halvings(b);
     return enqueue_flux<false>(&c, b);
 }
 

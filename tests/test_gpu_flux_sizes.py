@@ -280,3 +280,24 @@ def test_many_small_sets_other_calls(gpu_lib, ctx):
     assert census["sub_in_window"] > 4 * n
     for o in outs[1:]:
         assert np.array_equal(outs[0].cpu().numpy(), o.cpu().numpy(), equal_nan=True)
+
+
+@pytest.mark.parametrize("own", [False, True])
+@pytest.mark.parametrize("n_sets,n_times", [(1, 100), (3, 1009), (16, 130), (40, 300)])
+def test_few_sets_of_many_sub_samples(gpu_lib, ctx, n_sets, n_times, own):
+    # ranges halved by each set's n_ss: the same bits as each output on its own
+    from paper_2410_05408_amd import workloads as W
+    print(f"case: {n_sets} sets of {n_times} outputs of 1 to 64 sub-samples, own grids {own}", flush=True)
+    rng = np.random.default_rng(12)
+    p = W.walker_batch(n_sets=max(2, n_sets)).params[:, :n_sets]
+    p[W.T0] = 0.0
+    t = np.linspace(-0.25, 0.25, n_times)
+    ss, te = rng.integers(1, 65, n_sets).astype(np.int32), np.full(n_sets, 0.004)
+    ss[0] = 64
+    off = np.arange(n_sets + 1, dtype=np.int64) * n_times
+    w = W.Workload("few", np.ascontiguousarray(p), np.tile(t, n_sets) if own else t, off if own else None, ss, te, {})
+    got = flux(gpu_lib, ctx, w)
+    n = n_sets * n_times
+    alone = W.Workload("alone", np.ascontiguousarray(np.repeat(p, n_times, axis=1)), np.tile(t, n_sets), np.arange(n + 1, dtype=np.int64),
+                       np.repeat(ss, n_times), np.repeat(te, n_times), {})
+    assert np.array_equal(got, flux(gpu_lib, ctx, alone))
